@@ -1,0 +1,82 @@
+"""The calibration kernels at the sizes where they can go wrong: counts around
+a wave's 16 vectors and the block's 128, the sampled walk (over 512 vectors),
+coordinates that all fall into one bin, infinite inputs, and Gram matrices of
+low rank.
+
+Tolerances: the tables are fp64 inside and rounded to fp32 at the end, half an
+ulp of a level below 8 (2.4e-7); ebar and sigma are relative fp32 roundings
+(6e-8) of fp64 results."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_26110_amd as tq
+from oracle import oracle
+from paper_2603_26110_amd import synth
+
+pytestmark = pytest.mark.gpu
+INIT = synth.GAUSS_LEVELS_MAX1960
+
+
+def _keys(seed, H, n):
+    g = synth.rng(seed)
+    return np.ascontiguousarray(synth.keys(g, 1, 1, n, H, synth.outlier_channels(g, 1, H))[0, 0].transpose(1, 0, 2)), \
+        synth.rotations(g, 1, H)[0]
+
+
+def _d(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("rotate", [True, False])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 127, 128, 129, 511, 1029])
+def test_tables_and_ebar_at_every_remainder(n, rotate):
+    x, pi = _keys(900 + n, 2, n)
+    x[1, n // 2] = 0.0
+    got = tq.calibrate_lut(_d(x), _d(pi) if rotate else None, INIT)
+    eb = tq.calibrate_ebar(_d(x), got, _d(pi) if rotate else None).cpu().numpy()
+    got = got.cpu().numpy()
+    for h in range(2):
+        p = pi[h] if rotate else None
+        np.testing.assert_allclose(got[h], oracle.calibrate_lut(x[h], p, INIT), rtol=0, atol=5e-7)
+        assert eb[h] == pytest.approx(oracle.calibrate_ebar(x[h], p, got[h]), rel=2e-7)
+
+
+@pytest.mark.parametrize("n", [600, 2048])
+def test_tables_of_equal_coordinates(n):
+    # nine in ten coordinates are 0, the middle midpoint of the starting table:
+    # a bin that no window holds
+    g = synth.rng(31)
+    x = (g.standard_normal((2, n, 64)) * (g.random((2, n, 64)) < 0.1)).astype(np.float32)
+    x[1, :, 1:] = np.sign(x[1, :, 1:])                     # few values in all
+    got = tq.calibrate_lut(_d(x), None, INIT).cpu().numpy()
+    for h in range(2):
+        np.testing.assert_allclose(got[h], oracle.calibrate_lut(x[h], None, INIT), rtol=0, atol=5e-7)
+
+
+def _plain_lloyd(u, max_iter, tol):
+    """The iteration as it is defined, over all coordinates (NaN compares false throughout)."""
+    c = INIT.astype(np.float64)
+    for _ in range(max_iter):
+        t = 0.5 * (c[1:] + c[:-1])
+        idx = (u[:, None] > t).sum(1)
+        new = np.array([u[idx == k].mean() if np.any(idx == k) else c[k] for k in range(8)])
+        delta = np.nanmax(np.abs(new - c))
+        c = np.concatenate([[new[0]], np.sort(new[1:])]) if np.isnan(new[0]) else np.sort(new)
+        if delta < tol:
+            break
+    return c
+
+
+def test_tables_with_an_infinite_input():
+    # its vector's norm is infinite: that coordinate is NaN, the others 0
+    g = synth.rng(32)
+    x = g.standard_normal((1, 200, 64)).astype(np.float32)
+    x[0, 7, 3] = np.inf
+    with np.errstate(invalid="ignore"):
+        xd = x[0].astype(np.float64)
+        u = xd * (8.0 / np.sqrt((xd * xd).sum(1, keepdims=True)))
+        ref = _plain_lloyd(u.ravel(), 10, 1e-7)
+    got = tq.calibrate_lut(_d(x), None, INIT, max_iter=10).cpu().numpy()[0]
+    assert np.isnan(got[0]) and np.isnan(ref[0])
+    np.testing.assert_allclose(got[1:], ref[1:], rtol=0, atol=5e-7)
