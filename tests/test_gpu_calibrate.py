@@ -80,3 +80,21 @@ def test_tables_with_an_infinite_input():
     got = tq.calibrate_lut(_d(x), None, INIT, max_iter=10).cpu().numpy()[0]
     assert np.isnan(got[0]) and np.isnan(ref[0])
     np.testing.assert_allclose(got[1:], ref[1:], rtol=0, atol=5e-7)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 63, 65, 257, 1025])
+def test_rotation_at_every_remainder_and_rank(n):
+    x, _ = _keys(950 + n, 3, n)
+    x[2] *= 1e-18                                          # (squares of fp64 entries far below fp32's range)
+    pi, sg = (a.cpu().numpy().astype(np.float64) for a in tq.calibrate_rotation(_d(x)))
+    for h in range(3):
+        ref = np.zeros(64)
+        s = np.linalg.svd(x[h].astype(np.float64), compute_uv=False)
+        ref[:len(s)] = s
+        np.testing.assert_allclose(pi[h] @ pi[h].T, np.eye(64), atol=5e-7)
+        # singular values of the Gram matrix: its entries are exact to 2^-53 of sigma_0^2
+        np.testing.assert_allclose(sg[h], ref, rtol=1e-6, atol=3e-7 * ref[0])
+        y = x[h].astype(np.float64) @ pi[h].T
+        gram = y.T @ y
+        assert np.max(np.abs(gram - np.diag(np.diag(gram)))) <= 1e-6 * ref[0] ** 2
+        assert np.all(np.take_along_axis(pi[h], np.abs(pi[h]).argmax(1)[:, None], 1) > 0)
