@@ -59,7 +59,6 @@
 namespace tq {
 
 constexpr float kLazyRescale = 8.0f;   // log2 headroom before the max is raised
-constexpr int kXcds = 8;
 
 // Block barrier that orders LDS only. __syncthreads() also waits for every
 // outstanding global load of the wave (its release fence covers global

@@ -23,6 +23,7 @@ constexpr int kDim = 64;
 constexpr int kTile = 64;
 constexpr int kTileBytes = 2048;   // 64 slots x 32 bytes
 constexpr int kPairs = 32;
+constexpr int kXcds = 8;           // blocks go to the 8 XCDs round-robin
 
 // Flags (values fixed by the public header).
 constexpr uint32_t kVRotate = 1u << 0;
@@ -65,17 +66,13 @@ __device__ __forceinline__ int64_t tile_half_offset(int64_t tile, int c, int r) 
 // Fixed-order binary32 steps of the quantizer for one vector held in registers
 // (this file is compiled with -ffp-contract=off and correctly rounded sqrtf and
 // division, the HIP defaults; fmaf is the only fused operation)
-// by one lane: the norm and residual-norm fma chains run over i ascending and
-// the projected sign of row i is an fma chain over k ascending, so any kernel
-// that calls this on the same x^ produces the same bits.
-//   xh[64]   rotated vector (overwritten by the residual r)
-//   L        ascending table and its midpoints (0.5f * (c_m + c_{m+1}))
-//   S        64 x 64 projection in LDS (row-major); unused unless sign_mode == 1
-//   sign_mode 0 none, 1 projected (S r), 2 per element (r), 3 projected with
-//            the signs set by the caller (g is computed and stored, no bits)
-//   words[8] out: with KEY_WORDS the key word format (index of dimension 8w+j
-//            in bits 3j..3j+2, its sign in bit 24+j), else nibble words
-//            (idx | sign << 3 in bits 4j..4j+3)
+// by one lane: the norm and residual-norm fma chains run over i ascending, so
+// any kernel that calls this on the same x^ produces the same bits.
+//   xh[64]   rotated vector over `scale` (overwritten by the residual r)
+//   scale    a power of two, which no rounding of these steps depends on
+//   thr, lev the table's midpoints {t0, t2, t4, t6, t1, t3, t5} and its levels,
+//            in LDS
+//   words[8] out: index of dimension 8w+j in bits width*j of word w
 // The eight levels and seven midpoints of one table as named register values.
 // Named members (no arrays) keep the level choice a chain of selects between
 // registers; an array indexed inside a loop gets folded into an indexed load
@@ -137,15 +134,15 @@ __device__ __forceinline__ float nearest_level(float u, const Levels& L, float c
 // write VCC only and each is used at once, so no lane mask stays live across
 // the elements of a vector (64 unrolled select chains keep so many masks
 // live that they spill).
-__device__ __forceinline__ uint32_t level_index(float u, const Levels& L, const float* thr_even) {
-  // The count is the length of the prefix of thresholds below u (they are
-  // non-decreasing), found in three steps: b2 = [t3 < u], b1 =
-  // [t(b2 ? 5 : 1) < u] and b0 = [t(4 b2 + 2 b1) < u], each bit added into
-  // the count by a carry (a NaN u compares false throughout, like the
-  // count). The second threshold is selected in registers (t1 and t5 as
-  // vector operands: a select that reads VCC cannot also read a scalar);
-  // the third, t(2 i) for i = 2 b2 + b1, is read from thr_even = {t0, t2, t4,
-  // t6} in LDS.
+// The count is the length of the prefix of thresholds below u (they are
+// non-decreasing), found in three steps: b2 = [t3 < u], b1 =
+// [t(b2 ? 5 : 1) < u] and b0 = [t(4 b2 + 2 b1) < u], each bit added into
+// the count by a carry (a NaN u compares false throughout, like the
+// count). The second threshold is selected in registers (t1 and t5 as
+// vector operands: a select that reads VCC cannot also read a scalar);
+// the third, t(2 i) for i = 2 b2 + b1, is read from {t0, t2, t4, t6} in LDS.
+// level_half gives i, level_full the count from i and that threshold.
+__device__ __forceinline__ uint32_t level_half(float u, float t1, float t3, float t5) {
   uint32_t i;
   float ta;
   asm("v_cmp_lt_f32 vcc, %2, %5\n\t"
@@ -154,9 +151,12 @@ __device__ __forceinline__ uint32_t level_index(float u, const Levels& L, const 
       "v_cmp_lt_f32 vcc, %1, %5\n\t"
       "v_addc_co_u32 %0, vcc, %0, %0, vcc"
       : "=&v"(i), "=&v"(ta)
-      : "s"(L.t3), "v"(L.t1), "v"(L.t5), "v"(u)
+      : "v"(t3), "v"(t1), "v"(t5), "v"(u)
       : "vcc");
-  const float tb = thr_even[i];
+  return i;
+}
+
+__device__ __forceinline__ uint32_t level_full(float u, uint32_t i, float tb) {
   asm("v_cmp_lt_f32 vcc, %1, %2\n\t"
       "v_addc_co_u32 %0, vcc, %0, %0, vcc"
       : "+v"(i)
@@ -165,59 +165,61 @@ __device__ __forceinline__ uint32_t level_index(float u, const Levels& L, const 
   return i;
 }
 
+// Sixteen values loaded before any of them is used: the wave waits for its
+// LDS reads once per sixteen.
+__device__ __forceinline__ void arrive16(float (&v)[16]) {
+  asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
+               "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15]));
+}
+
 struct QuantOut {
   uint32_t n16, g16;
   float g;                 // ||r|| in binary32 (before the fp16 store)
 };
 
-template <bool KEY_WORDS>
-__device__ __forceinline__ QuantOut quantize_lane(float (&xh)[kDim], const Levels& L, const float* lev,
-                                                  const float* thr_even, const float* S, int sign_mode,
-                                                  uint32_t (&words)[8]) {
+__device__ __forceinline__ QuantOut quantize_lane(float (&xh)[kDim], float scale, const float* thr, const float* lev,
+                                                  uint32_t width, uint32_t (&words)[8]) {
   float s = 0.0f;
 #pragma unroll
   for (int i = 0; i < kDim; ++i) s = fmaf(xh[i], xh[i], s);
   const float n = sqrtf(s);
   const float inv = (n == 0.0f) ? 0.0f : 8.0f / n;
+  const float t1 = thr[4], t3 = thr[5], t5 = thr[6];
 #pragma unroll
-  for (int w = 0; w < 8; ++w) words[w] = 0u;
+  for (int i0 = 0; i0 < kDim; i0 += 16) {
+    uint32_t idx[16];
+    float rd[16];
 #pragma unroll
-  for (int i = 0; i < kDim; ++i) {
-    const float u = xh[i] * inv;
-    const uint32_t idx = level_index(u, L, thr_even);
-    const float lv = lev[idx];   // the level c[idx], from the table in LDS
-    words[i >> 3] |= idx << ((KEY_WORDS ? 3 : 4) * (i & 7));
-    xh[i] = u - lv;   // residual r_i
+    for (int j = 0; j < 16; ++j) {
+      xh[i0 + j] *= inv;               // u_i
+      idx[j] = level_half(xh[i0 + j], t1, t3, t5);
+      rd[j] = thr[idx[j]];
+    }
+    arrive16(rd);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      idx[j] = level_full(xh[i0 + j], idx[j], rd[j]);
+      rd[j] = lev[idx[j]];             // the level c[idx]
+    }
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      uint32_t word = idx[8 * w + 7];
+#pragma unroll
+      for (int j = 6; j >= 0; --j) word = (word << width) | idx[8 * w + j];
+      asm volatile("" : "+v"(word));   // (packed here: a later place would keep all indices live)
+      words[(i0 >> 3) + w] = word;
+    }
+    arrive16(rd);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) xh[i0 + j] -= rd[j];   // residual r_i
   }
   float gs = 0.0f;
 #pragma unroll
   for (int i = 0; i < kDim; ++i) gs = fmaf(xh[i], xh[i], gs);
   const float g = sqrtf(gs);
-  uint64_t sbits = 0;
-  if (sign_mode == 1) {
-    for (int i = 0; i < kDim; ++i) {
-      float acc = 0.0f;
-      const float4* row = reinterpret_cast<const float4*>(S + i * kDim);
-#pragma unroll
-      for (int k4 = 0; k4 < kDim / 4; ++k4) {
-        const float4 sv = row[k4];
-        acc = fmaf(sv.x, xh[4 * k4 + 0], acc);
-        acc = fmaf(sv.y, xh[4 * k4 + 1], acc);
-        acc = fmaf(sv.z, xh[4 * k4 + 2], acc);
-        acc = fmaf(sv.w, xh[4 * k4 + 3], acc);
-      }
-      sbits |= (uint64_t)((acc < 0.0f) ? 0u : 1u) << i;
-    }
-  } else if (sign_mode == 2) {
-#pragma unroll
-    for (int i = 0; i < kDim; ++i) sbits |= (uint64_t)((xh[i] < 0.0f) ? 0u : 1u) << i;
-  }
-#pragma unroll
-  for (int i = 0; i < kDim; ++i)
-    words[i >> 3] |= (uint32_t)((sbits >> i) & 1u) << (KEY_WORDS ? 24 + (i & 7) : 4 * (i & 7) + 3);
   QuantOut o;
-  o.n16 = store_norm(n);
-  o.g16 = (sign_mode == 0) ? 0u : store_norm(g);
+  o.n16 = store_norm(n * scale);
+  o.g16 = store_norm(g);
   o.g = g;
   return o;
 }

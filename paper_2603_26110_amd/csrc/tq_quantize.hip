@@ -3,11 +3,11 @@
 // prefill steps 1, 3, 4; Sec. 3.3; Sec. 3.4; Sec. 4.2).
 //
 // Two kernels:
-//   quantize_tiles_kernel   for prefill-sized T: 64 tokens per wave; the
-//                           rotations x^ = Pi x' of the wave's 64 x 64 block
-//                           and the projections S r run on the matrix cores
-//                           (fp16 MFMA on hi/lo parts), one lane per token
-//                           runs the quantizer steps.
+//   quantize_tiles_kernel   for prefill-sized T: the keys and values of 32
+//                           tokens per wave; the rotations x^ = Pi x' of
+//                           these 64 vectors and the projections S r run on
+//                           the matrix cores (fp16 MFMA on hi/lo parts), one
+//                           lane per vector runs the quantizer steps.
 //   quantize_vectors_kernel one wave per vector (one lane per dimension; the
 //                           key and the value of a token-head in parallel), for
 //                           decode-step appends with small T; its rotation is
@@ -16,6 +16,9 @@
 // the fixed binary32 order of quantize_lane / quantize_wave, so identical x^
 // give identical bits; for raw inputs the two rotations sum in different
 // orders, so a code can differ where x^ sits within rounding of a threshold.
+#include <algorithm>
+#include <type_traits>
+
 #include "tq_append.hpp"
 #include "tq_device.hpp"
 #include "tq_internal.hpp"
@@ -44,80 +47,105 @@ hipError_t launch_rope_table(float* cs, int positions, double base, hipStream_t 
 
 // ------------------------------------------- matrix-core products of 64 rows
 // Two dense 64 x 64 x 64 products per wave run on the matrix cores: the
-// rotation x^ = Pi x' of the wave's 64 tokens and the QJL projection S r of
-// their residuals. Both use v_mfma_f32_32x32x16_f16 (fp16 inputs, fp32 sums)
-// with each fp32 operand split into fp16 parts hi = fp16(v), lo = fp16(v - hi)
-// and three products hi*hi + hi*lo + lo*hi, which carries a product to about
-// 2^-21 relative. Each token's vector is first scaled by a power of two
-// (exact) so that its largest entry lies in [1, 2), and each row of S
-// likewise, which keeps the parts in fp16's range; the results are scaled
-// back (exact) or compared with equally scaled bounds.
+// rotation x^ = Pi x' of the keys and values of the wave's 32 tokens and the
+// QJL projection S r of their residuals. Both use v_mfma_f32_32x32x16_f16
+// (fp16 inputs, fp32 sums) with each fp32 operand split into fp16 parts
+// hi = fp16(v), lo = fp16(v - hi) and three products hi*hi + hi*lo + lo*hi,
+// which carries a product to about 2^-21 relative. Each vector is first scaled
+// by a power of two (exact) so that its largest entry lies in [1, 2), and each
+// row of S likewise, which keeps the parts in fp16's range. Values in fp16 are
+// their own high part: they are neither scaled nor split, and have no low part.
 // Instruction layout (lane l, n = l % 32, h = l / 32; verified on gfx950):
 //   A lane values A[n][8h + j], B lane values B[8h + j][n] (j = 0..7),
 //   D register r D[8 (r/4) + 4h + r%4][n].
-// Step q (0..3) contracts k = 16q + 8h + j: a lane's B values at step q are 8
-// consecutive dimensions of its token (one 16-byte load of fp16 input) and
-// its A values 8 consecutive columns of a row of the staged matrix (one
+// Block 0 of the B operand (nb = 0) holds the 32 keys and block 1 the 32
+// values. Step q (0..3) contracts k = 16q + 8h + j: a lane's B values at step
+// q are 8 consecutive dimensions of its token (one 16-byte load of fp16 input)
+// and its A values 8 consecutive columns of a row of the staged matrix (one
 // 16-byte LDS read per part). The result leaves lane half h the dimensions
-// {8q + 4h + j, j < 4} of its two tokens (32 nb + n, nb = 0, 1); one
-// v_permlane32_swap per register pair then hands lane l all 64 values of
-// token l.
+// {8q + 4h + j, j < 4} of key n and of value n; one v_permlane32_swap per
+// register pair then hands lane l < 32 all 64 values of key l and lane l >= 32
+// those of value l - 32.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
-// Halfs per staged row: the 16-byte reads of 16 rows (36 dwords apart) fall
-// on all 64 banks once.
-constexpr int kHPitch = 72;
+constexpr int kGroup = 32;                   // tokens per wave
 
-struct SplitOps {
-  half8 hi[2][4], lo[2][4];   // [token block nb][step q]
-};
+// 16-byte chunk c (columns 8c .. 8c + 7) of row r of a staged 64 x 64 matrix
+// of fp16 lies at chunk position c ^ (r / 2 % 8) of its row: the 16 rows read
+// together fall on all 64 banks once, without padding.
+__device__ __forceinline__ int staged_at(int r, int c) { return r * kDim + ((c ^ ((r >> 1) & 7)) << 3); }
 
+// Blocks of a pair of products: D[mb][nb], rows 32 mb .. and vectors of block nb.
+typedef f32x16 Blocks[2][2];
+
+// hi = fp16(v sc), lo = fp16(v sc - hi), sc a power of two (v sc exact): one
+// mixed-precision fma each, as pairs in one register. (The s_nop: a matrix
+// instruction may not read a register in the two wait states after a vector
+// instruction wrote it, and the compiler does not look into the block.)
 __device__ __forceinline__ void split8(const float* v, float sc, half8& hi, half8& lo) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float x = v[j] * sc;
-    const _Float16 a = (_Float16)x;
-    hi[j] = a;
-    lo[j] = (_Float16)(x - (float)a);
-  }
+  uint32_t h[4], l[4];
+  asm("v_fma_mixlo_f16 %0, %8, %16, 0\n\t"
+      "v_fma_mixlo_f16 %1, %10, %16, 0\n\t"
+      "v_fma_mixlo_f16 %2, %12, %16, 0\n\t"
+      "v_fma_mixlo_f16 %3, %14, %16, 0\n\t"
+      "v_fma_mixhi_f16 %0, %9, %16, 0\n\t"
+      "v_fma_mixhi_f16 %1, %11, %16, 0\n\t"
+      "v_fma_mixhi_f16 %2, %13, %16, 0\n\t"
+      "v_fma_mixhi_f16 %3, %15, %16, 0\n\t"
+      "v_fma_mixlo_f16 %4, %8, %16, -%0 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixlo_f16 %5, %10, %16, -%1 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixlo_f16 %6, %12, %16, -%2 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixlo_f16 %7, %14, %16, -%3 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %4, %9, %16, -%0 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %5, %11, %16, -%1 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %6, %13, %16, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %7, %15, %16, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "s_nop 1"
+      : "=&v"(h[0]), "=&v"(h[1]), "=&v"(h[2]), "=&v"(h[3]), "=&v"(l[0]), "=&v"(l[1]), "=&v"(l[2]), "=&v"(l[3])
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "v"(sc));
+  hi = __builtin_bit_cast(half8, make_uint4(h[0], h[1], h[2], h[3]));
+  lo = __builtin_bit_cast(half8, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
 // 2^(1 - e) for m = f 2^e, f in [0.5, 1): m times it lies in [1, 2); 1 for m = 0.
 __device__ __forceinline__ float unit_scale(float m) {
-  if (!(m > 0.0f)) return 1.0f;
-  int e;
-  frexpf(m, &e);
-  return ldexpf(1.0f, 1 - e);
+  const float s = ldexpf(1.0f, 1 - __builtin_amdgcn_frexp_expf(m));
+  return m > 0.0f ? s : 1.0f;
 }
 
-// acc[mb][nb] = rows 32 mb .. 32 mb + 31 of the staged matrix times the
-// wave's token blocks, as hi*hi + hi*lo + lo*hi.
-__device__ __forceinline__ void split_products(const SplitOps& b, const _Float16* mh, const _Float16* ml,
-                                               int lane, f32x16 (&acc)[2][2]) {
-  const int n = lane & 31, hh = lane >> 5;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[0][0][r] = 0.0f; acc[1][0][r] = 0.0f; acc[0][1][r] = 0.0f; acc[1][1][r] = 0.0f; }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    int o = n * kHPitch + 16 * q + 8 * hh;
-    asm volatile("" : "+v"(o));
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      const half8 ah = *reinterpret_cast<const half8*>(mh + o + 32 * mb * kHPitch);
-      const half8 al = *reinterpret_cast<const half8*>(ml + o + 32 * mb * kHPitch);
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b.hi[nb][q], acc[mb][nb], 0, 0, 0);
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b.lo[nb][q], acc[mb][nb], 0, 0, 0);
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, b.hi[nb][q], acc[mb][nb], 0, 0, 0);
-      }
-    }
-  }
+// Step Q of acc[mb] (+)= rows 32 mb .. of the matrix (parts mh, ml) times block
+// 0 (b0h, b0l) and, with TWO, block 1 (b1h and, with LO1, b1l); step 0 starts
+// from zero. The blocks take turns, so that a product does not wait for the
+// one before it.
+template <int Q, bool TWO, bool LO1>
+__device__ __forceinline__ void product_step(Blocks& acc, int mb, const _Float16* mh, const _Float16* ml, int lane,
+                                             half8 b0h, half8 b0l, half8 b1h, half8 b1l) {
+  int o = staged_at(lane & 31, 2 * Q + (lane >> 5));
+  asm volatile("" : "+v"(o));
+  // (rows 32 apart have the same chunk order)
+  const half8 ah = *reinterpret_cast<const half8*>(mh + o + 32 * mb * kDim);
+  const half8 al = *reinterpret_cast<const half8*>(ml + o + 32 * mb * kDim);
+  const f32x16 zero = {};
+  acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b0h, Q == 0 ? zero : acc[mb][0], 0, 0, 0);
+  if (TWO) acc[mb][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b1h, Q == 0 ? zero : acc[mb][1], 0, 0, 0);
+  acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b0l, acc[mb][0], 0, 0, 0);
+  if (TWO && LO1) acc[mb][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b1l, acc[mb][1], 0, 0, 0);
+  acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, b0h, acc[mb][0], 0, 0, 0);
+  if (TWO) acc[mb][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, b1h, acc[mb][1], 0, 0, 0);
 }
 
-// D blocks -> lane l holds all 64 rows for token l (column l of the block pair).
-__device__ __forceinline__ void to_lane_per_token(f32x16 (&acc)[2][2], float (&out)[kDim]) {
+// f(Q) for Q = 0 .. 3 as compile-time constants.
+template <class F>
+__device__ __forceinline__ void four_steps(F f) {
+  f(std::integral_constant<int, 0>{});
+  f(std::integral_constant<int, 1>{});
+  f(std::integral_constant<int, 2>{});
+  f(std::integral_constant<int, 3>{});
+}
+
+// D blocks -> lane l holds all 64 rows of its vector (key l, or value l - 32).
+__device__ __forceinline__ void to_lane_per_vector(Blocks& acc, float (&out)[kDim]) {
 #pragma unroll
   for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -130,426 +158,703 @@ __device__ __forceinline__ void to_lane_per_token(f32x16 (&acc)[2][2], float (&o
     }
 }
 
-// Loads the lane's values x'[16q + 8h + j] of tokens j0 + n (nb = 0) and
-// j0 + 32 + n (nb = 1), applies RoPE (keys; both pairings keep a pair inside
-// the lane: (2m, 2m + 1) inside a group of 8, (d, d + 32) in groups q and
-// q + 2), scales each token by a power of two and splits it. Returns the
-// lane's token scale (of token j0 + lane, for scaling the result back).
+// A lane's part of key and value j0 + n as loaded (dimensions 16q + 8h + j),
+// and the key's RoPE (cos, sin).
 template <bool F16>
-__device__ __forceinline__ float load_split_rows(SplitOps& ops, const QuantArgs& a, const void* src, int li,
-                                                 int b, int h, int j0, int Tb, int lane, bool rope) {
-  const int n = lane & 31, hh = lane >> 5;
-  const bool half = (a.flags & kRopeHalf) != 0;
-  float sc_nb[2];
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
-    const int j = j0 + 32 * nb + n;
-    const int pos = a.pos0[b] + j;
-    const bool ok = j < Tb && (!rope || (pos >= 0 && pos < a.rope_positions));
-    const int64_t row = ((((int64_t)li * a.B + b) * a.T + j) * a.H + h) * kDim;
-    float xv[32];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int d0 = 16 * q + 8 * hh;
-      if (F16) {
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (ok) w = *reinterpret_cast<const uint4*>(reinterpret_cast<const __half*>(src) + row + d0);
-        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          xv[8 * q + 2 * p] = half_bits_to_float(ww[p]);
-          xv[8 * q + 2 * p + 1] = half_bits_to_float(ww[p] >> 16);
-        }
-      } else {
-        float4 f0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), f1 = f0;
-        if (ok) {
-          f0 = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + row + d0);
-          f1 = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + row + d0 + 4);
-        }
-        xv[8 * q + 0] = f0.x; xv[8 * q + 1] = f0.y; xv[8 * q + 2] = f0.z; xv[8 * q + 3] = f0.w;
-        xv[8 * q + 4] = f1.x; xv[8 * q + 5] = f1.y; xv[8 * q + 6] = f1.z; xv[8 * q + 7] = f1.w;
-      }
-    }
-    if (rope && ok) {
-      const float4* cs4 = reinterpret_cast<const float4*>(a.rope_cs + (int64_t)pos * 2 * kPairs);
-      if (!half) {
-        // pairs m = (16q + 8h)/2 + p, p = 0..3: (cos, sin) of two pairs per float4
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int pp = 0; pp < 2; ++pp) {
-            const float4 c = cs4[(16 * q + 8 * hh) / 4 + pp];
-            float* g = &xv[8 * q + 4 * pp];
-            const float x0 = g[0], x1 = g[1], x2 = g[2], x3 = g[3];
-            g[0] = x0 * c.x - x1 * c.y; g[1] = x0 * c.y + x1 * c.x;
-            g[2] = x2 * c.z - x3 * c.w; g[3] = x2 * c.w + x3 * c.z;
-          }
-      } else {
-        // pair (d, d + 32), d = 16q + 8h + j for q < 2, angle index d
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-          for (int j4 = 0; j4 < 4; ++j4) {
-            const float4 c = cs4[(16 * q + 8 * hh) / 2 + j4];   // (c, s) of d and d + 1
-#pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2) {
-              const int jj = 2 * j4 + t2;
-              const float cc = t2 ? c.z : c.x, ss = t2 ? c.w : c.y;
-              const float xa = xv[8 * q + jj], xb = xv[8 * (q + 2) + jj];
-              xv[8 * q + jj] = xa * cc - xb * ss;
-              xv[8 * (q + 2) + jj] = xa * ss + xb * cc;
-            }
-          }
-      }
-    }
-    float m = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) m = fmaxf(m, fabsf(xv[k]));
-    m = fmaxf(m, __shfl_xor(m, 32, 64));   // the token's other 32 values sit in lane l ^ 32
-    sc_nb[nb] = unit_scale(m);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) split8(&xv[8 * q], sc_nb[nb], ops.hi[nb][q], ops.lo[nb][q]);
-  }
-  return hh ? sc_nb[1] : sc_nb[0];
-}
+struct RawRows {
+  uint4 k[F16 ? 4 : 8], v[F16 ? 4 : 8];
+  float4 cs[8];
+};
 
-// x^ of token j0 + lane in out[64] (Pi staged as fp16 parts).
+// A token past the sequence's end or with a position outside the table is
+// loaded at the nearest valid one (its result is not stored), so that no load
+// waits for a branch.
 template <bool F16>
-__device__ __forceinline__ void rotate_tokens(float (&out)[kDim], const QuantArgs& a, const void* src,
-                                              const _Float16* pih, const _Float16* pil, int li, int b, int h,
-                                              int j0, int Tb, int lane, bool rope) {
-  SplitOps ops;
-  const float sc = load_split_rows<F16>(ops, a, src, li, b, h, j0, Tb, lane, rope);
-  f32x16 acc[2][2];
-  split_products(ops, pih, pil, lane, acc);
-  to_lane_per_token(acc, out);
-  const float inv = 1.0f / sc;   // a power of two: exact
-#pragma unroll
-  for (int d = 0; d < kDim; ++d) out[d] *= inv;
-}
-
-// Projected QJL sign bits of the wave's 64 residuals (lane l: r of token
-// j0 + l): bit i = !(p_i < 0) for p_i the binary32 fma chain over k
-// ascending of S[i][k] r_k (the exact quantizer step). p~ = (sigma_i S_i) .
-// (s r) comes from the matrix cores (sigma_i, s: the row's and the token's
-// power-of-two scales). Any evaluation of it there is within
-// 2^-17.3 ||sigma_i S_i|| ||s r|| of its exact value (2^-21 per split
-// product, the fp16 spacing below the unit-sized entries, and fp32 sums of
-// 64 terms) and the chain within 2^-18 of that, so where
-// |p~_i| > 2^-14 ||sigma_i S_i|| ||s r|| the signs agree; the coordinates
-// inside that band are recomputed with the chain from S in memory.
-// The residuals reach the B layout through v_permlane32_swap pairs
-// (16q + j, 16q + 8 + j) and go back the same way (a swap undoes itself).
-__device__ __forceinline__ uint64_t projected_signs(float (&x)[kDim], float g, const _Float16* sh,
-                                                    const _Float16* sl, const float* s_Sn, const float* S,
-                                                    int lane) {
-  const int n = lane & 31, hh = lane >> 5;
-  float m = 0.0f;
-#pragma unroll
-  for (int k = 0; k < kDim; ++k) m = fmaxf(m, fabsf(x[k]));
-  const float sc = unit_scale(m);                    // token l's scale
-  const float sc_other = __shfl_xor(sc, 32, 64);     // token l ^ 32's
-  const float sc0 = hh ? sc_other : sc, sc1 = hh ? sc : sc_other;   // tokens n, 32 + n
-  // Step q's operands are built just before its products, from swapped
-  // copies (x keeps the lane-per-token layout for the chain below).
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[0][0][r] = 0.0f; acc[1][0][r] = 0.0f; acc[0][1][r] = 0.0f; acc[1][1][r] = 0.0f; }
+__device__ __forceinline__ void load_rows(RawRows<F16>& raw, const QuantArgs& a, int64_t row, int pos, int lane) {
+  const int hh = lane >> 5;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    float b0[8], b1[8];
+    if (F16) {
+      raw.k[q] = *reinterpret_cast<const uint4*>(reinterpret_cast<const __half*>(a.k) + row + 16 * q + 8 * hh);
+    } else {
+      const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(a.k) + row + 16 * q + 8 * hh);
+      raw.k[2 * q] = p[0];
+      raw.k[2 * q + 1] = p[1];
+    }
+  }
+  // (cos, sin) of two pairs per float4: pairs 8q + 4h + {0..3} of (2m, 2m + 1),
+  // or the angles 16q + 8h + {0..7}, q < 2, of (d, d + 32)
+  const bool half = (a.flags & kRopeHalf) != 0;
+  const float4* cs4 = reinterpret_cast<const float4*>(a.rope_cs + (int64_t)pos * 2 * kPairs) + (half ? 4 : 2) * hh;
+  if (half) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) raw.cs[e] = cs4[8 * (e >> 2) + (e & 3)];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) raw.cs[e] = cs4[4 * (e >> 1) + (e & 1)];
+  }
+  if (a.flags & kVRotate) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (F16) {
+        raw.v[q] = *reinterpret_cast<const uint4*>(reinterpret_cast<const __half*>(a.v) + row + 16 * q + 8 * hh);
+      } else {
+        const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(a.v) + row + 16 * q + 8 * hh);
+        raw.v[2 * q] = p[0];
+        raw.v[2 * q + 1] = p[1];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < (F16 ? 4 : 8); ++q) raw.v[q] = make_uint4(0, 0, 0, 0);
+  }
+}
+
+template <bool F16>
+__device__ __forceinline__ void unpack_rows(float (&xv)[32], const uint4* raw) {
+#pragma unroll
+  for (int e = 0; e < (F16 ? 4 : 8); ++e) {
+    const uint32_t w[4] = {raw[e].x, raw[e].y, raw[e].z, raw[e].w};
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      if (F16) {
+        xv[8 * e + 2 * p] = half_bits_to_float(w[p]);
+        xv[8 * e + 2 * p + 1] = half_bits_to_float(w[p] >> 16);
+      } else {
+        xv[4 * e + p] = __uint_as_float(w[p]);
+      }
+    }
+  }
+}
+
+// x c + y for x the half HI of an fp16 pair; NEG: x c - y.
+template <int HI, bool NEG = false>
+__device__ __forceinline__ float mix(uint32_t pair, float c, float y) {
+  float r;
+  if constexpr (HI && NEG)
+    asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pair), "v"(c), "v"(y));
+  else if constexpr (HI)
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pair), "v"(c), "v"(y));
+  else if constexpr (NEG)
+    asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pair), "v"(c), "v"(y));
+  else
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pair), "v"(c), "v"(y));
+  return r;
+}
+
+// RoPE of a lane's part of a key (both pairings keep a pair inside the lane:
+// (2m, 2m + 1) inside a group of 8, (d, d + 32) in groups q and q + 2):
+// x'_a = x_a c - x_b s, x'_b = x_a s + x_b c, as fma(x_a, c, -(x_b s)) and
+// fma(x_a, s, x_b c). fp16 inputs enter the fmas as they are.
+template <bool F16>
+__device__ __forceinline__ void rope_rows(float (&xv)[32], const uint4* raw, const float4 (&cs)[8], bool half) {
+  if constexpr (F16) {
+    uint32_t w[16];                            // pairs of dimensions 2i, 2i + 1 of the lane's 32
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { w[4 * q] = raw[q].x; w[4 * q + 1] = raw[q].y; w[4 * q + 2] = raw[q].z; w[4 * q + 3] = raw[q].w; }
+    if (!half) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float c = (i & 1) ? cs[i >> 1].z : cs[i >> 1].x, s = (i & 1) ? cs[i >> 1].w : cs[i >> 1].y;
+        xv[2 * i] = mix<0, true>(w[i], c, mix<1>(w[i], s, 0.0f));
+        xv[2 * i + 1] = mix<0>(w[i], s, mix<1>(w[i], c, 0.0f));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {            // angles of dimensions 2i and 2i + 1
+        const float4 c = cs[i];
+        xv[2 * i] = mix<0, true>(w[i], c.x, mix<0>(w[8 + i], c.y, 0.0f));
+        xv[16 + 2 * i] = mix<0>(w[i], c.y, mix<0>(w[8 + i], c.x, 0.0f));
+        xv[2 * i + 1] = mix<1, true>(w[i], c.z, mix<1>(w[8 + i], c.w, 0.0f));
+        xv[17 + 2 * i] = mix<1>(w[i], c.w, mix<1>(w[8 + i], c.z, 0.0f));
+      }
+    }
+    return;
+  }
+  unpack_rows<F16>(xv, raw);
+  if (!half) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float4 c = cs[e];
+      const float x0 = xv[4 * e], x1 = xv[4 * e + 1], x2 = xv[4 * e + 2], x3 = xv[4 * e + 3];
+      xv[4 * e] = fmaf(x0, c.x, -(x1 * c.y)); xv[4 * e + 1] = fmaf(x0, c.y, x1 * c.x);
+      xv[4 * e + 2] = fmaf(x2, c.z, -(x3 * c.w)); xv[4 * e + 3] = fmaf(x2, c.w, x3 * c.z);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float4 c = cs[e];
+      const float xa = xv[2 * e], xb = xv[16 + 2 * e], ya = xv[2 * e + 1], yb = xv[16 + 2 * e + 1];
+      xv[2 * e] = fmaf(xa, c.x, -(xb * c.y)); xv[16 + 2 * e] = fmaf(xa, c.y, xb * c.x);
+      xv[2 * e + 1] = fmaf(ya, c.z, -(yb * c.w)); xv[16 + 2 * e + 1] = fmaf(ya, c.w, yb * c.z);
+    }
+  }
+}
+
+// The scale that brings a vector's largest entry into [1, 2).
+__device__ __forceinline__ float vector_scale(const float (&xv)[32]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 32; ++k) m = fmaxf(m, fabsf(xv[k]));
+  return unit_scale(fmaxf(m, __shfl_xor(m, 32, 64)));   // (the other 32 entries sit in lane l ^ 32)
+}
+
+// x^ of the lane's vector in out[64] (Pi staged as fp16 parts), over the
+// returned power of two: the vector's scale, left in, since scaling by a power
+// of two changes no rounding of the norm and of u = 8 x^ / n, and taken out
+// (1 returned) where some vector's scale is so far from 1 that squares could
+// leave fp32's range.
+template <bool F16>
+__device__ __forceinline__ float rotate_rows(float (&out)[kDim], const RawRows<F16>& raw, const _Float16* pih,
+                                             const _Float16* pil, bool half, int lane) {
+  half8 kh[4], kl[4], vh[4], vl[4];
+  float sk, sv = 1.0f;
+  {
+    float xv[32];
+    rope_rows<F16>(xv, raw.k, raw.cs, half);
+    sk = vector_scale(xv);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) split8(&xv[8 * q], sk, kh[q], kl[q]);
+  }
+  if constexpr (F16) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) vh[q] = __builtin_bit_cast(half8, raw.v[q]);
+  } else {
+    float xv[32];
+    unpack_rows<F16>(xv, raw.v);
+    sv = vector_scale(xv);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) split8(&xv[8 * q], sv, vh[q], vl[q]);
+  }
+  Blocks acc;
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+    four_steps([&](auto q) {
+      product_step<q, true, !F16>(acc, mb, pih, pil, lane, kh[q], kl[q], vh[q], F16 ? vh[q] : vl[q]);
+    });
+  to_lane_per_vector(acc, out);
+  const float inv = 1.0f / (lane < 32 ? sk : sv);   // a power of two: exact
+  if (__builtin_amdgcn_ballot_w64(!(inv >= 0x1p-40f && inv <= 0x1p40f)) == 0) return inv;
+#pragma unroll
+  for (int d = 0; d < kDim; ++d) out[d] *= inv;
+  return 1.0f;
+}
+
+// A vector as it is (pre-rotated inputs, values without TQ_V_ROTATE).
+template <bool F16>
+__device__ __forceinline__ void load_vector(float (&x)[kDim], const void* src, int64_t row) {
+#pragma unroll
+  for (int i = 0; i < kDim; i += 8) {
+    if (F16) {
+      const uint4 w = *reinterpret_cast<const uint4*>(reinterpret_cast<const __half*>(src) + row + i);
+      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        x[i + 2 * p] = half_bits_to_float(ww[p]);
+        x[i + 2 * p + 1] = half_bits_to_float(ww[p] >> 16);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; u += 4) {
+        const float4 f = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + row + i + u);
+        x[i + u] = f.x; x[i + u + 1] = f.y; x[i + u + 2] = f.z; x[i + u + 3] = f.w;
+      }
+    }
+  }
+}
+
+// A load at a wave-uniform address as a scalar load.
+template <class T>
+__device__ __forceinline__ T scalar_load(const T* p) {
+  return *(const __attribute__((address_space(4))) T*)p;
+}
+
+// (word << 1) | sign of v.
+__device__ __forceinline__ uint32_t push_sign(uint32_t word, float v) {
+  return __builtin_amdgcn_alignbit(word, __float_as_uint(v), 31);
+}
+
+// min(|a|, |b|, m). (Not inline assembly: its operands come from matrix
+// instructions, whose latency the compiler waits out only for its own.)
+__device__ __forceinline__ float min_abs3(float a, float b, float m) { return fminf(fminf(fabsf(a), fabsf(b)), m); }
+
+// Nibble k of the low 16 bits to the low nibble of byte k.
+__device__ __forceinline__ uint32_t nibbles_to_bytes(uint32_t x) {
+  x = (x | (x << 8)) & 0x00FF00FFu;
+  return (x | (x << 4)) & 0x0F0F0F0Fu;
+}
+
+// Projected QJL sign bits of the wave's residuals (lane l: r of its key, or
+// with BOTH its key or value): bit i = !(p_i < 0) for p_i the binary32 fma
+// chain over k ascending of S[i][k] r_k (the exact quantizer step).
+// p~ = (sigma_i S_i) . (s r) comes from the matrix cores (sigma_i, s: the
+// row's and the vector's power-of-two scales; s brings ||r|| = g into [1, 2)).
+// Any evaluation of it there is within 2^-17.3 ||sigma_i S_i|| ||s r|| of its
+// exact value (2^-20.4 for the split products, 2^-21 for the fp16 spacing
+// below 2^-14, 2^-18.2 for 28 fp32 additions per sum, truncated at worst) and
+// the chain within 2^-18 of that, 2^-16.6 in all, so where
+// |p~_i| > 2^-16 max_i ||sigma_i S_i|| ||s r|| the signs agree. The smallest
+// |p~_i| tells whether any coordinate lies inside that band (snmax: the
+// largest row norm, infinite if a row is not finite); only then are the rows
+// found, and recomputed with the chain from S in memory for all the wave's
+// vectors (every lane's bit of a recomputed row is the chain's).
+// The residuals reach the B layout through v_permlane32_swap pairs
+// (16q + j, 16q + 8 + j). With keys alone the result stays where it is: lane
+// half h has the signs of the dimensions 8w + 4h + j of key n, which the
+// halves exchange as one register.
+template <bool BOTH>
+__device__ __forceinline__ uint64_t projected_signs(float (&x)[kDim], float g, const _Float16* sh, const _Float16* sl,
+                                                    float snmax, const float* S, int lane) {
+  const float sc = unit_scale(g);
+  const float sc_other = __shfl_xor(sc, 32, 64), g_other = __shfl_xor(g, 32, 64);
+  const float sk = lane < 32 ? sc : sc_other, sv = lane < 32 ? sc_other : sc;   // of key n and value n
+  // Step q's operands are built just before its products; the swaps are undone
+  // only where the chain below needs the vectors again.
+  auto swap_pairs = [&](int q) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[16 * q + j]),
                                                        __float_as_uint(x[16 * q + 8 + j]), false, false);
-      b0[j] = __uint_as_float(sw[0]);   // token n, dimension 16q + 8h + j
-      b1[j] = __uint_as_float(sw[1]);   // token 32 + n, dimension 16q + 8h + j
+      x[16 * q + j] = __uint_as_float(sw[0]);       // key n, dimension 16q + 8h + j
+      x[16 * q + 8 + j] = __uint_as_float(sw[1]);   // value n, dimension 16q + 8h + j
     }
-    half8 h0, l0, h1, l1;
-    split8(b0, sc0, h0, l0);
-    split8(b1, sc1, h1, l1);
-    int o = n * kHPitch + 16 * q + 8 * hh;
-    asm volatile("" : "+v"(o));
+  };
+  Blocks acc;
+  four_steps([&](auto q) {
+    half8 h0, l0, h1{}, l1{};
+    swap_pairs(q);
+    split8(&x[16 * q], sk, h0, l0);
+    if (BOTH) split8(&x[16 * q + 8], sv, h1, l1);
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      const half8 ah = *reinterpret_cast<const half8*>(sh + o + 32 * mb * kHPitch);
-      const half8 al = *reinterpret_cast<const half8*>(sl + o + 32 * mb * kHPitch);
-      acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, h0, acc[mb][0], 0, 0, 0);
-      acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, l0, acc[mb][0], 0, 0, 0);
-      acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, h0, acc[mb][0], 0, 0, 0);
-      acc[mb][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, h1, acc[mb][1], 0, 0, 0);
-      acc[mb][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, l1, acc[mb][1], 0, 0, 0);
-      acc[mb][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, h1, acc[mb][1], 0, 0, 0);
-    }
-  }
-  // the result reaches lane l (token l) one register pair at a time and is
-  // tested at once (no 64-value copy of it is held)
-  uint64_t bits = 0, flagged = 0;
-  const float gb = g * sc * 0x1p-14f;
+    for (int mb = 0; mb < 2; ++mb) product_step<q, BOTH, BOTH>(acc, mb, sh, sl, lane, h0, l0, h1, l1);
+  });
+  uint64_t bits, any = 0;
+  if constexpr (BOTH) {
+    float p[kDim];
+    to_lane_per_vector(acc, p);
+    const float band = snmax * (g * sc) * 0x1p-16f;
+    float least[4];                            // of dimensions 16 e .. 16 e + 15
+    uint32_t neg[2];
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+    for (int e = 3; e >= 0; --e) {
+      least[e] = INFINITY;
+      if (e & 1) neg[e >> 1] = 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[mb][0][r]),
-                                                       __float_as_uint(acc[mb][1][r]), false, false);
-      const int d = 32 * mb + 8 * (r >> 2) + (r & 3);
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int i = d + 4 * e;
-        const float pv = __uint_as_float(sw[e]);
-        const bool sure = fabsf(pv) > s_Sn[i] * gb;
-        bits |= (uint64_t)((sure && !(pv < 0.0f)) ? 1u : 0u) << i;
-        flagged |= (uint64_t)(sure ? 0u : 1u) << i;
+      for (int i = 16 * e + 15; i > 16 * e; i -= 2) {
+        neg[e >> 1] = push_sign(push_sign(neg[e >> 1], p[i]), p[i - 1]);
+        least[e] = min_abs3(p[i], p[i - 1], least[e]);
       }
     }
-  // rows inside the band, any lane: the fixed-order chain (wave-uniform row)
-  uint64_t any = flagged;
+    bits = ~(((uint64_t)neg[1] << 32) | neg[0]);
+    const float low = fminf(fminf(least[0], least[1]), fminf(least[2], least[3]));
+    if (__builtin_amdgcn_ballot_w64(!(low > band)) != 0) {
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t lo = __shfl_xor((uint32_t)any, o, 64), hi = __shfl_xor((uint32_t)(any >> 32), o, 64);
-    any |= ((uint64_t)hi << 32) | lo;
+      for (int e = 0; e < 4; ++e) {
+        if (__builtin_amdgcn_ballot_w64(!(least[e] > band)) == 0) continue;
+#pragma unroll
+        for (int i = 16 * e; i < 16 * e + 16; ++i)
+          any |= (uint64_t)(__builtin_amdgcn_ballot_w64(!(fabsf(p[i]) > band)) != 0) << i;
+      }
+    }
+  } else {
+    const float band = snmax * ((lane < 32 ? g : g_other) * sk) * 0x1p-16f;
+    float least[4];                            // of registers 8 e .. 8 e + 7
+    uint32_t neg = 0;                          // nibble w: dimensions 8 w + 4 h + j
+#pragma unroll
+    for (int e = 3; e >= 0; --e) {
+      least[e] = INFINITY;
+#pragma unroll
+      for (int r = 8 * e + 7; r > 8 * e; r -= 2) {
+        const float hi = acc[r >> 4][0][r & 15], lo = acc[(r - 1) >> 4][0][(r - 1) & 15];
+        neg = push_sign(push_sign(neg, hi), lo);
+        least[e] = min_abs3(hi, lo, least[e]);
+      }
+    }
+    const uint32_t other = __shfl_xor(neg, 32, 64);
+    bits = ~(((uint64_t)(nibbles_to_bytes(neg >> 16) | (nibbles_to_bytes(other >> 16) << 4)) << 32) |
+             (nibbles_to_bytes(neg & 0xFFFFu) | (nibbles_to_bytes(other & 0xFFFFu) << 4)));
+    const float low = fminf(fminf(least[0], least[1]), fminf(least[2], least[3]));
+    if (__builtin_amdgcn_ballot_w64(!(low > band)) != 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (__builtin_amdgcn_ballot_w64(!(least[e] > band)) == 0) continue;
+#pragma unroll
+        for (int r = 8 * e; r < 8 * e + 8; ++r) {
+          const uint64_t in = __builtin_amdgcn_ballot_w64(!(fabsf(acc[r >> 4][0][r & 15]) > band));
+          const int d = 8 * (r >> 2) + (r & 3);
+          any |= (uint64_t)((uint32_t)in != 0u) << d | (uint64_t)((uint32_t)(in >> 32) != 0u) << (d + 4);
+        }
+      }
+    }
+  }
+  // rows inside the band: the fixed-order chain (wave-uniform row), over
+  // vectors as the swaps left them: with keys alone, lane half h holds the
+  // dimensions 16q + 8h + j, and the running sum of key n moves between lanes
+  // n and n + 32 every eight elements (both halves run along; lane n ends with
+  // the chain).
+  if constexpr (BOTH) {
+    if (any) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) swap_pairs(q);
+    }
   }
   while (any) {
     const int i = __builtin_ctzll(any);
     any &= any - 1;
-    if ((flagged >> i) & 1ull) {
-      const float4* row = reinterpret_cast<const float4*>(S + i * kDim);
-      float acc_i = 0.0f;
+    float acc_i = 0.0f;
 #pragma unroll
-      for (int k4 = 0; k4 < kDim / 4; ++k4) {
-        const float4 sv = row[k4];
-        acc_i = fmaf(sv.x, x[4 * k4 + 0], acc_i);
-        acc_i = fmaf(sv.y, x[4 * k4 + 1], acc_i);
-        acc_i = fmaf(sv.z, x[4 * k4 + 2], acc_i);
-        acc_i = fmaf(sv.w, x[4 * k4 + 3], acc_i);
-      }
-      bits |= (uint64_t)((acc_i < 0.0f) ? 0u : 1u) << i;
+    for (int k = 0; k < kDim; ++k) {
+      if (!BOTH && k > 0 && k % 8 == 0) acc_i = __shfl_xor(acc_i, 32, 64);
+      acc_i = fmaf(scalar_load(S + i * kDim + k), x[BOTH ? k : 16 * (k / 16) + k % 8], acc_i);
     }
+    if (!BOTH) acc_i = __shfl_xor(acc_i, 32, 64);
+    bits = (bits & ~(1ull << i)) | ((uint64_t)((acc_i < 0.0f) ? 0u : 1u) << i);
   }
   return bits;
 }
 
-// ----------------------------------------------------- lane-per-token kernel
-// Block: 4 waves x 64 tokens of one (layer, sequence, head). Grid:
-// x = ceil(T/256), y = B*H, z = nlayers. LDS: Pi (pitch 68) for the
-// rotations, S (row-major, read by the quantizer as broadcasts) and one
-// 64 x 8 word buffer per wave for the V transpose.
-// Three waves per SIMD (168 registers, no spills for the default flags: the
-// key words and the value words wait in LDS while their signs are computed,
-// per-lane slot facts are recomputed where used, a level's index is found by
-// a three-step search whose comparisons each write VCC only). Asking the
-// compiler for four waves per SIMD gives 232 registers (two waves) instead:
-// the two rotations' and the projection's 64-value results and their
-// operands do not fit in 128.
-template <bool F16, bool VQJL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void quantize_tiles_kernel(QuantArgs a) {
-  __shared__ __attribute__((aligned(16))) _Float16 s_pih[kDim * kHPitch];   // Pi, fp16 parts
-  __shared__ __attribute__((aligned(16))) _Float16 s_pil[kDim * kHPitch];
-  __shared__ __attribute__((aligned(16))) _Float16 s_sh[kDim * kHPitch];    // sigma_i S_i, fp16 parts
-  __shared__ __attribute__((aligned(16))) _Float16 s_sl[kDim * kHPitch];
-  __shared__ float s_Sn[kDim];                                               // ||sigma_i S_i||
-  __shared__ uint32_t s_vt[4][kDim * 8];
-  __shared__ float s_lev[2][8];                                              // K and V levels
-  __shared__ float s_thr[2][4];                                              // their t0, t2, t4, t6
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// 8 x 8 nibbles: nibble e of word d <- nibble d of word e.
+__device__ __forceinline__ void transpose_nibbles(uint32_t (&m)[8]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {                // halves: words e and e + 4
+    const uint32_t x = m[e], y = m[e + 4];
+    m[e] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+    m[e + 4] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+  }
+#pragma unroll
+  for (int e0 = 0; e0 < 4; ++e0) {             // bytes: words e and e + 2, e = 0, 1, 4, 5
+    const int e = (e0 & 1) + 4 * (e0 >> 1);
+    const uint32_t x = m[e], y = m[e + 2];
+    m[e] = __builtin_amdgcn_perm(y, x, 0x06020400u);
+    m[e + 2] = __builtin_amdgcn_perm(y, x, 0x07030501u);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {             // nibbles: words e and e + 1
+    const uint32_t x = m[e], y = m[e + 1];
+    m[e] = (x & 0x0F0F0F0Fu) | ((y & 0x0F0F0F0Fu) << 4);
+    m[e + 1] = ((x >> 4) & 0x0F0F0F0Fu) | (y & 0xF0F0F0F0u);
+  }
+}
 
-  const int h = blockIdx.y % a.H, b = blockIdx.y / a.H, li = blockIdx.z;
-  const int l = a.layer0 + li;
-  const int64_t lh = (int64_t)l * a.H + h;
-  const bool rotated = (a.flags & kInputRotated) != 0;
+// All four bits of nibble j set where bit j of the low byte is.
+__device__ __forceinline__ uint32_t nibble_mask(uint32_t m) {
+  m = (m | (m << 12)) & 0x000F000Fu;
+  m = (m | (m << 6)) & 0x03030303u;
+  m = (m | (m << 3)) & 0x11111111u;
+  return m * 15u;
+}
+
+// The groups of 32 tokens of a (layer, head), numbered through the sequences
+// in order. In a ragged call sequence b has ceil(T_b / 32) of them; lane i of
+// a wave then holds the running count of groups up to sequence first + i of a
+// window of 64 sequences, and a group's sequence is found by one ballot (the
+// window moves where the group lies outside it).
+struct GroupCursor {
+  int first, base, end;   // the window's first sequence; groups before and up to the end of the window
+  int upto, own;          // per lane: groups up to and of sequence first + lane
+
+  __device__ __forceinline__ void window(const QuantArgs& a, int f, int before, int lane) {
+    first = f;
+    base = before;
+    own = f + lane < a.B ? (min(max(a.tokens[f + lane], 0), a.T) + kGroup - 1) / kGroup : 0;
+    upto = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int w = __shfl_up(upto, o, 64);
+      upto += lane >= o ? w : 0;
+    }
+    upto += before;
+    end = __builtin_amdgcn_readlane(upto, 63);
+  }
+};
+
+// ---------------------------------------------------- lane-per-vector kernel
+// One block of 12 waves per compute unit takes an equal, contiguous share of
+// the call's groups of 32 tokens, numbered (layer, head) by (layer, head). It
+// stages S once and Pi and the tables of up to four (layer, head)s at a time;
+// its waves then take the groups of these in turn, with no barrier between
+// (layer, head)s.
+//
+// What bounds it: the vector ALU, 1,660 instructions per group at three waves
+// per SIMD (168 registers), and what three waves leave uncovered of their load
+// and LDS latencies. Keys and values side by side in one wave (half the lanes
+// each) make one instruction stream of both, halve the registers of the
+// projected signs (only keys have them), and a group's keys and values end
+// together; that the value lanes run the residual steps unused costs less.
+// Four waves per SIMD would need 128 registers: the compiler then spills 40,
+// and the spills' 78 MB of traffic cost more than the fourth wave gives (131
+// against 112 us in blocks of 4 waves).
+// fp16, 20 heads: 1024 tokens of 33 layers 102 us, of one layer 12.9 us, one
+// layer of 64 sequences of 50 to 1024 tokens 112 us; 127, 20.6 and 210 us in
+// blocks of 4 waves of which each took 64 tokens of one sequence, first the
+// keys and then the values: partly filled blocks and a chain twice as long.
+constexpr int kPackWaves = 12;
+constexpr int kPackThreads = kPackWaves * 64;
+constexpr int kPackHeads = 4;       // (layer, head)s staged at a time
+constexpr int kComputeUnits = 256;
+constexpr int kVtPitch = 9;         // words per token in a wave's transpose buffer
+constexpr int kVtDims8 = 36;        // words per 8 dimensions in it, after the transpose
+
+template <bool F16, bool VQJL, bool ROTATED>
+__global__ __launch_bounds__(kPackThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic div_seq, DivMagic div_h) {
+  __shared__ __attribute__((aligned(16))) _Float16 s_pih[kPackHeads][kDim * kDim];   // Pi, fp16 parts
+  __shared__ __attribute__((aligned(16))) _Float16 s_pil[kPackHeads][kDim * kDim];
+  __shared__ __attribute__((aligned(16))) _Float16 s_sh[kDim * kDim];                // sigma_i S_i, fp16 parts
+  __shared__ __attribute__((aligned(16))) _Float16 s_sl[kDim * kDim];
+  __shared__ float s_Sn[kDim];                                                        // ||sigma_i S_i||
+  __shared__ __attribute__((aligned(16))) uint32_t s_vt[kPackWaves][8 * kVtDims8];
+  __shared__ float s_lev[kPackHeads][2][8];                                           // K and V levels
+  __shared__ float s_thr[kPackHeads][2][8];                                           // their t0, t2, t4, t6, t1, t3, t5
+  __shared__ int s_asc[kPackHeads][2];                                                // strictly ascending
+  // The thread's and the lane's number from a copy that the compiler cannot
+  // carry over: what is derived from them is formed where it is used, instead
+  // of staying live (and spilled) through the loops.
+  auto thread_of = [&]() {
+    int t;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"((int)threadIdx.x));
+    return t;
+  };
+  auto lane_of = [&]() { return thread_of() & 63; };
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr bool rotated = ROTATED;
   const bool paper = (a.flags & kQjlPaper) != 0;
-  const int vsign = VQJL ? (paper ? 2 : 1) : 0;   // (a V sign pass is compiled only where asked for)
 
-  // Pi and S staged as fp16 parts, with the rows of S scaled by powers of
-  // two sigma_i and their norms: thread t takes row t / 4, columns
-  // 16 (t % 4) .. 16 (t % 4) + 15 of both (all eight 16-byte loads issued
-  // together); a row's four threads combine their maxima and sums by shuffles.
-  {
-    const int r = threadIdx.x >> 2, c0 = 16 * (threadIdx.x & 3);
-    const float4* pi4 = reinterpret_cast<const float4*>(a.pi + lh * kDim * kDim) + r * 16 + c0 / 4;
-    const float4* s4 = reinterpret_cast<const float4*>(a.qjl_s) + r * 16 + c0 / 4;
-    float pv[16], sv[16];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float4 p4 = pi4[u], q4 = s4[u];
-      pv[4 * u] = p4.x; pv[4 * u + 1] = p4.y; pv[4 * u + 2] = p4.z; pv[4 * u + 3] = p4.w;
-      sv[4 * u] = q4.x; sv[4 * u + 1] = q4.y; sv[4 * u + 2] = q4.z; sv[4 * u + 3] = q4.w;
+  // ---- the block's share of the groups. Blocks go to the 8 XCDs round-robin;
+  // each XCD gets one contiguous eighth of the shares.
+  GroupCursor cur{};
+  int per_head = a.B * groups_per_seq;
+  if (a.tokens) {
+    cur.window(a, 0, 0, lane_of());
+    per_head = cur.end;
+    for (int f = 64; f < a.B; f += 64) {
+      cur.window(a, f, per_head, lane_of());
+      per_head = cur.end;
     }
-    float mx = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) mx = fmaxf(mx, fabsf(sv[k]));
-    mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-    const float sig = unit_scale(mx);        // row r's scale (the same in its four threads)
-    float ss = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const float v = sv[k] * sig;
-      ss = fmaf(v, v, ss);
-    }
-    ss += __shfl_xor(ss, 1, 64);
-    ss += __shfl_xor(ss, 2, 64);
-    if ((threadIdx.x & 3) == 0) s_Sn[r] = sqrtf(ss);   // bounds the guard band only
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const float sa = sv[k] * sig;
-      const _Float16 ph = (_Float16)pv[k], sh = (_Float16)sa;
-      s_pih[r * kHPitch + c0 + k] = ph;
-      s_pil[r * kHPitch + c0 + k] = (_Float16)(pv[k] - (float)ph);
-      s_sh[r * kHPitch + c0 + k] = sh;
-      s_sl[r * kHPitch + c0 + k] = (_Float16)(sa - (float)sh);
-    }
-    if (threadIdx.x < 16) s_lev[threadIdx.x >> 3][threadIdx.x & 7] =
-        ((threadIdx.x >> 3) ? a.lut_v : a.lut_k)[lh * 8 + (threadIdx.x & 7)];
+    if (per_head == 0) return;
   }
-  const Levels Lk = load_levels(a.lut_k + lh * 8);
-  const Levels Lv = load_levels(a.lut_v + lh * 8);
-  if (threadIdx.x == 0) {
-    s_thr[0][0] = Lk.t0; s_thr[0][1] = Lk.t2; s_thr[0][2] = Lk.t4; s_thr[0][3] = Lk.t6;
-    s_thr[1][0] = Lv.t0; s_thr[1][1] = Lv.t2; s_thr[1][2] = Lv.t4; s_thr[1][3] = Lv.t6;
-  }
-  __syncthreads();
+  const uint32_t share = (blockIdx.x % kXcds) * ((uint32_t)blocks / kXcds) + blockIdx.x / kXcds;
+  const uint64_t total = (uint64_t)per_head * (uint32_t)(a.H * a.nlayers);
+  const uint64_t begin = total * share / (uint32_t)blocks;
+  int64_t left = (int64_t)(total * (share + 1) / (uint32_t)blocks - begin);
+  uint32_t head = (uint32_t)(begin / (uint32_t)per_head);       // nlayers x H, relative to layer0
+  int g0 = (int)(begin - (uint64_t)head * (uint32_t)per_head);  // the share starts at its group g0
 
-  const int j0 = blockIdx.x * 256 + wave * kTile;
-  // the sequence's tokens: all T, or its own count in a ragged call
-  const int Tb = a.tokens ? min(max(a.tokens[b], 0), a.T) : a.T;
-  if (j0 >= Tb) return;                   // wave-uniform; no barrier follows
-  // a (layer, head) whose K or V table is not strictly ascending is not written
-  if (!levels_ascending(Lk) || !levels_ascending(Lv)) return;
-  const int64_t sbase = a.slot0[b];
-  const int pbase = a.pos0[b];
-  // The lane's token facts (written or not, its slot, its input row) are
-  // recomputed where used, from an index the compiler cannot carry over,
-  // so that no 64-bit per-lane value stays live through the products.
-  auto lane_of = [&]() {
-    int ln;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(ln) : "v"((int)threadIdx.x));
-    return ln & 63;
-  };
-  auto ok_of = [&](int jl) {
-    const int64_t sl = sbase + jl;
-    const int ps = pbase + jl;
-    return jl < Tb && sl >= 0 && sl < a.slots && (rotated || (ps >= 0 && ps < a.rope_positions));
-  };
-  auto row_of = [&](int jl) { return ((((int64_t)li * a.B + b) * a.T + jl) * a.H + h) * kDim; };
-
-  uint8_t* kreg = a.k_codes + lh * a.slots * 32;
-  uint8_t* vreg = a.v_codes + lh * a.slots * 32;
-
-  // ---- K: RoPE and rotation, or a pre-rotated input as is
-  float x[kDim];
-  if (rotated) {
-    const int jl = j0 + lane;
-    const bool okl = ok_of(jl);
-    const int64_t row = row_of(jl);
-#pragma unroll
-    for (int i = 0; i < kDim; ++i) x[i] = okl ? load_in(a.k, row + i, false) : 0.0f;
-  } else {
-    rotate_tokens<F16>(x, a, a.k, s_pih, s_pil, li, b, h, j0, Tb, lane, true);
-  }
-  uint32_t kw[8];
-  const QuantOut qk = quantize_lane<true>(x, Lk, s_lev[0], s_thr[0], nullptr, paper ? 2 : 3, kw);
-  if (!paper) {
-    // the key words wait in this wave's transpose buffer while the signs are
-    // computed (registers)
-    uint32_t* s_k = s_vt[wave];
-#pragma unroll
-    for (int w = 0; w < 8; ++w) s_k[lane * 8 + w] = kw[w];
-    const uint64_t sb = projected_signs(x, qk.g, s_sh, s_sl, s_Sn, a.qjl_s, lane);
-    const int lk = lane_of();
-#pragma unroll
-    for (int w = 0; w < 8; ++w) kw[w] = s_k[lk * 8 + w] | (uint32_t)((sb >> (8 * w)) & 0xFFu) << 24;
-  }
-  const int jk = j0 + lane_of();
-  const int64_t slot = sbase + jk;
-  if (ok_of(jk)) {
-    const int64_t tile = slot >> 6;
-    const int r = (int)(slot & 63);
-    *reinterpret_cast<uint4*>(kreg + tile_half_offset(tile, 0, r)) = make_uint4(kw[0], kw[1], kw[2], kw[3]);
-    *reinterpret_cast<uint4*>(kreg + tile_half_offset(tile, 1, r)) = make_uint4(kw[4], kw[5], kw[6], kw[7]);
-    // [n_k, g_k] now (the V half of the slot's scalars follows), so that
-    // nothing of the key stays live through the value's products
-    reinterpret_cast<uint32_t*>(a.scalars + (lh * a.slots + slot) * 4)[0] = qk.n16 | (qk.g16 << 16);
-  }
-
-  // ---- V (no RoPE): rotated like K unless TQ_V_ROTATE is off. The V loads
-  // are not hoisted above the key's stores (registers, occupancy).
-  asm volatile("" ::: "memory");
-  if (!rotated && (a.flags & kVRotate)) {
-    rotate_tokens<F16>(x, a, a.v, s_pih, s_pil, li, b, h, j0, Tb, lane, false);
-  } else {
-    const int jl = j0 + lane;
-    const bool okl = ok_of(jl);
-    const int64_t row = row_of(jl);
-#pragma unroll
-    for (int i = 0; i < kDim; ++i) x[i] = okl ? load_in(a.v, row + i, F16) : 0.0f;
-  }
-  uint32_t vw[8];
-  const QuantOut qv = quantize_lane<false>(x, Lv, s_lev[1], s_thr[1], nullptr, (VQJL && !paper) ? 3 : vsign, vw);
-  // V is stored dimension-major: transpose the wave's 64 x 64 nibbles through
-  // its LDS buffer (token-major words in, one dimension per lane out). The
-  // words go there first; the projected signs of the value residual, where
-  // asked for, are merged in there (registers).
-  uint32_t* s_w = s_vt[wave];
-#pragma unroll
-  for (int w = 0; w < 8; ++w) s_w[lane * 8 + w] = vw[w];
-  if (VQJL && !paper) {
-    const uint64_t sb = projected_signs(x, qv.g, s_sh, s_sl, s_Sn, a.qjl_s, lane);
-    const int lv = lane_of();
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      uint32_t add = 0;
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) add |= (uint32_t)((sb >> (8 * w + jj)) & 1ull) << (4 * jj + 3);
-      s_w[lv * 8 + w] |= add;
+  bool first = true;
+  while (left > 0) {
+    // (layer, head)s head .. head + nheads - 1: `count` groups from g0 of the first one on
+    const int64_t reach = (left + g0 + per_head - 1) / per_head;
+    const int nheads = (int)min(reach, (int64_t)kPackHeads);
+    const int count = (int)min(left, (int64_t)nheads * per_head - g0);
+    const int64_t lh0 = (int64_t)a.layer0 * a.H + head;
+    if (!first) __syncthreads();               // the heads before are done with
+    for (int u = thread_of(); u < nheads * 512; u += kPackThreads) {
+      const int hd = u >> 9, r = (u & 511) >> 3, c = u & 7;
+      const float4* src = reinterpret_cast<const float4*>(a.pi + (lh0 + hd) * kDim * kDim + r * kDim + 8 * c);
+      const float4 x = src[0], y = src[1];
+      const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+      half8 hi, lo;
+      split8(v, 1.0f, hi, lo);
+      *reinterpret_cast<half8*>(s_pih[hd] + staged_at(r, c)) = hi;
+      *reinterpret_cast<half8*>(s_pil[hd] + staged_at(r, c)) = lo;
     }
-  }
-  const int jv = j0 + lane_of();
-  const bool ok = ok_of(jv);
-  if (ok) reinterpret_cast<uint32_t*>(a.scalars + (lh * a.slots + sbase + jv) * 4)[1] = qv.n16 | (qv.g16 << 16);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const uint64_t okmask = __ballot(ok);
-  if (okmask == ~0ull && ((sbase + j0) & 7) == 0) {
-    // all 64 tokens, starting at a word boundary: eight whole words per
-    // dimension, nibble jj of word k from token 8k + jj
-    const int i = lane;
-    const int wsel = i >> 3, sh = 4 * (i & 7);
-    const int64_t g_first = (sbase + j0) >> 3;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      uint32_t word = 0;
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) word |= ((s_w[(8 * k + jj) * 8 + wsel] >> sh) & 15u) << (4 * jj);
-      const int64_t G = g_first + k;
-      const int64_t tile = G >> 3;
-      const int c = (int)((G & 7) >> 2);
-      *reinterpret_cast<uint32_t*>(vreg + tile_half_offset(tile, c, i) + (G & 3) * 4) = word;
+    if (const int t = thread_of(); t < 2 * nheads) {
+      const int hd = t >> 1, v = t & 1;
+      const Levels L = load_levels((v ? a.lut_v : a.lut_k) + (lh0 + hd) * 8);
+      float* lev = s_lev[hd][v];
+      float* thr = s_thr[hd][v];
+      lev[0] = L.c0; lev[1] = L.c1; lev[2] = L.c2; lev[3] = L.c3;
+      lev[4] = L.c4; lev[5] = L.c5; lev[6] = L.c6; lev[7] = L.c7;
+      thr[0] = L.t0; thr[1] = L.t2; thr[2] = L.t4; thr[3] = L.t6; thr[4] = L.t1; thr[5] = L.t3; thr[6] = L.t5;
+      s_asc[hd][v] = levels_ascending(L) ? 1 : 0;
     }
-  } else if (okmask != 0) {
-    const int i = lane;   // dimension handled by this lane
-    const int64_t sA = sbase + j0;           // slot of token j0
-    const int64_t g_first = sA >> 3, g_last = (sA + 63) >> 3;
-    for (int64_t G = g_first; G <= g_last; ++G) {
-      uint32_t word = 0, mask = 0;
+    // The rows of S scaled by powers of two sigma_i, and their norms, by the
+    // last four waves: four threads per row, which combine their maxima and
+    // sums by shuffles.
+    if (const int t = thread_of() - (kPackThreads - 256); first && t >= 0) {
+      const int r = t >> 2, c0 = 16 * (t & 3);
+      const float4* s4 = reinterpret_cast<const float4*>(a.qjl_s) + r * 16 + c0 / 4;
+      float sv[16];
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        const int64_t tau = G * 8 + jj - sA;
-        if (tau >= 0 && tau < 64 && ((okmask >> tau) & 1ull)) {
-          const uint32_t nib = (s_w[tau * 8 + (i >> 3)] >> (4 * (i & 7))) & 15u;
-          word |= nib << (4 * jj);
-          mask |= 15u << (4 * jj);
+      for (int u = 0; u < 4; ++u) {
+        const float4 q4 = s4[u];
+        sv[4 * u] = q4.x; sv[4 * u + 1] = q4.y; sv[4 * u + 2] = q4.z; sv[4 * u + 3] = q4.w;
+      }
+      float mx = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) mx = fmaxf(mx, fabsf(sv[k]));
+      mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
+      const float sig = unit_scale(mx);        // row r's scale (the same in its four threads)
+      float ss = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const float v = sv[k] * sig;
+        ss = fmaf(v, v, ss);
+      }
+      ss += __shfl_xor(ss, 1, 64);
+      ss += __shfl_xor(ss, 2, 64);
+      if ((t & 3) == 0) s_Sn[r] = sqrtf(ss);   // bounds the guard band only
+#pragma unroll
+      for (int k = 0; k < 16; k += 8) {
+        half8 hi, lo;
+        split8(sv + k, sig, hi, lo);
+        *reinterpret_cast<half8*>(s_sh + staged_at(r, (c0 + k) >> 3)) = hi;
+        *reinterpret_cast<half8*>(s_sl + staged_at(r, (c0 + k) >> 3)) = lo;
+      }
+    }
+    first = false;
+    __syncthreads();
+    float snmax = s_Sn[lane_of()];
+    snmax = snmax < INFINITY ? snmax : INFINITY;   // (NaN: a row that is not finite)
+    snmax = wave_max(snmax);
+
+    for (int item = wave; item < count; item += kPackWaves) {
+      int group = g0 + item, hd = 0;
+      while (group >= per_head) { group -= per_head; ++hd; }   // (at most three times)
+      // a (layer, head) whose K or V table is not strictly ascending is not written
+      if (!__builtin_amdgcn_readfirstlane(s_asc[hd][0] & s_asc[hd][1])) continue;
+      const int64_t lh = lh0 + hd;
+      const int li = (int)div_magic((int)head + hd, div_h), h = (int)head + hd - li * a.H;
+      // the group's sequence and tokens
+      int b, j0, Tb;
+      if (a.tokens) {
+        const int lane = lane_of();
+        if (group < cur.base) cur.window(a, 0, 0, lane);
+        while (group >= cur.end) cur.window(a, cur.first + 64, cur.end, lane);
+        const int i = __builtin_ctzll(__builtin_amdgcn_ballot_w64(cur.upto > group));
+        b = cur.first + i;
+        j0 = (group - __builtin_amdgcn_readlane(cur.upto - cur.own, i)) * kGroup;
+        Tb = min(max(scalar_load(a.tokens + b), 0), a.T);
+      } else {
+        b = (int)div_magic(group, div_seq);
+        j0 = (group - b * groups_per_seq) * kGroup;
+        Tb = a.T;
+      }
+      const int64_t sbase = scalar_load(a.slot0 + b);
+      const int pbase = scalar_load(a.pos0 + b);
+      uint8_t* kreg = a.k_codes + lh * a.slots * 32;
+      uint8_t* vreg = a.v_codes + lh * a.slots * 32;
+      int lane = lane_of();
+      bool is_v = lane >= 32;
+
+      // ---- x^: keys after RoPE and rotation, values rotated like them unless
+      // TQ_V_ROTATE is off; pre-rotated inputs as they are
+      float x[kDim];
+      float sc = 1.0f;
+      auto row_of = [&]() { return ((((int64_t)li * a.B + b) * a.T + min(j0 + (lane & 31), Tb - 1)) * a.H + h) * kDim; };
+      if (rotated) {
+        load_vector<false>(x, is_v ? a.v : a.k, row_of());
+      } else {
+        RawRows<F16> raw;
+        load_rows(raw, a, ((((int64_t)li * a.B + b) * a.T + min(j0 + (lane & 31), Tb - 1)) * a.H + h) * kDim,
+                  min(max(pbase + min(j0 + (lane & 31), Tb - 1), 0), a.rope_positions - 1), lane);
+        sc = rotate_rows(x, raw, s_pih[hd], s_pil[hd], (a.flags & kRopeHalf) != 0, lane);
+        if (!(a.flags & kVRotate)) {
+          if (is_v) {
+            load_vector<F16>(x, a.v, row_of());
+            sc = 1.0f;
+          }
         }
       }
-      if (mask) {
-        const int64_t tile = G >> 3;
-        const int c = (int)((G & 7) >> 2);
-        uint32_t* addr = reinterpret_cast<uint32_t*>(vreg + tile_half_offset(tile, c, i) + (G & 3) * 4);
-        store_v_word(addr, word, mask);
+
+      // ---- norm, levels, residual, signs: words of 8 dimensions, three bits
+      // each for keys and four for values
+      uint32_t words[8];
+      const QuantOut qo = quantize_lane(x, sc, s_thr[hd][is_v ? 1 : 0], s_lev[hd][is_v ? 1 : 0], is_v ? 4u : 3u, words);
+      uint64_t sb;
+      if (!paper) {
+        sb = projected_signs<VQJL>(x, qo.g, s_sh, s_sl, snmax, a.qjl_s, lane);
+      } else {
+        uint32_t neg[2] = {0u, 0u};            // (the sign of r: -0 is not below 0)
+#pragma unroll
+        for (int i = kDim - 1; i >= 0; --i) neg[i >> 5] = push_sign(neg[i >> 5], x[i] + 0.0f);
+        sb = ~(((uint64_t)neg[1] << 32) | neg[0]);
+      }
+
+      // The lane's token: written or not, its slot (formed here, so that
+      // nothing of it stays live through the products).
+      lane = lane_of();
+      is_v = lane >= 32;
+      const int jl = j0 + (lane & 31);
+      const int64_t base = sbase + j0;         // the slot of the group's first token
+      const int64_t slot = sbase + jl;
+      const bool ok = jl < Tb && slot >= 0 && slot < a.slots &&
+                      (rotated || (pbase + jl >= 0 && pbase + jl < a.rope_positions));
+      const uint32_t okmask = (uint32_t)__builtin_amdgcn_ballot_w64(ok);   // (both halves alike)
+      if (!is_v) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) words[w] |= (uint32_t)(sb >> (8 * w)) << 24;
+        if (ok) {
+          const int64_t ct = slot >> 6;
+          const int r = (int)(slot & 63);
+          *reinterpret_cast<uint4*>(kreg + tile_half_offset(ct, 0, r)) = make_uint4(words[0], words[1], words[2], words[3]);
+          *reinterpret_cast<uint4*>(kreg + tile_half_offset(ct, 1, r)) = make_uint4(words[4], words[5], words[6], words[7]);
+        }
+      } else if (VQJL) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) words[w] |= nibble_mask((uint32_t)(sb >> (8 * w)) & 0xFFu) & 0x88888888u;
+      }
+      if (ok) {
+        const uint32_t g16 = (VQJL || !is_v) ? qo.g16 : 0u;
+        reinterpret_cast<uint32_t*>(a.scalars + (lh * a.slots + slot) * 4)[is_v ? 1 : 0] = qo.n16 | (g16 << 16);
+      }
+
+      // ---- V is stored dimension-major: transpose the group's 32 x 64 nibbles
+      // through the wave's LDS buffer, in blocks of 8 tokens x 8 dimensions
+      // (lane (w, k) of the lower half: dimensions 8w .., tokens 8k ..), so
+      // that lane i gets the 16 bytes of dimension i. The pitches keep every
+      // access off a bank that another lane uses.
+      uint32_t* s_w = s_vt[wave];
+      if (is_v) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) s_w[(lane & 31) * kVtPitch + w] = words[w];
+      }
+      wave_sync_lds();
+      uint32_t m[8];
+      {
+        const int w = (lane & 31) >> 2, k = lane & 3;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m[e] = s_w[(8 * k + e) * kVtPitch + w];
+        transpose_nibbles(m);                  // m[d]: dimension 8w + d, token 8k + e in nibble e
+        wave_sync_lds();
+        if (!is_v) {
+#pragma unroll
+          for (int d = 0; d < 8; ++d) s_w[w * kVtDims8 + 4 * d + k] = m[d];
+        }
+      }
+      wave_sync_lds();
+      const uint4 dim = *reinterpret_cast<const uint4*>(s_w + (lane >> 3) * kVtDims8 + 4 * (lane & 7));
+      wave_sync_lds();                         // (the next group writes the buffer)
+      if (okmask == ~0u && (base & 31) == 0) {
+        *reinterpret_cast<uint4*>(vreg + tile_half_offset(base >> 6, (int)((base & 63) >> 5), lane)) = dim;
+      } else if (okmask != 0u) {
+        // any slots: words of 8 slots, of which `sh` precede the group's first token
+        const int sh = (int)(base & 7);
+        const int64_t G0 = (base - sh) / 8;    // (exact: base may be below 0)
+        const uint32_t d[6] = {0u, dim.x, dim.y, dim.z, dim.w, 0u};
+        const uint64_t in = (uint64_t)okmask << sh;
+#pragma unroll
+        for (int g = 0; g < 5; ++g) {
+          const uint32_t mask = nibble_mask((uint32_t)(in >> (8 * g)) & 0xFFu);
+          if (mask == 0u) continue;
+          const uint32_t word = sh ? (d[g + 1] << (4 * sh)) | (d[g] >> (32 - 4 * sh)) : d[g + 1];
+          const int64_t G = G0 + g;
+          store_v_word(reinterpret_cast<uint32_t*>(vreg + tile_half_offset(G >> 3, (int)((G & 7) >> 2), lane) + (G & 3) * 4),
+                       word, mask);
+        }
       }
     }
+    left -= count;
+    head += nheads;
+    g0 = 0;
   }
+}
+
+// Blocks of a launch: one per compute unit, or one per group where there are
+// fewer (an upper bound in a ragged call); a multiple of 8 (the XCDs).
+static int pack_blocks(int64_t groups) {
+  return (int)((std::min<int64_t>(groups, kComputeUnits) + kXcds - 1) / kXcds * kXcds);
 }
 
 // ----------------------------------------------- wave-per-vector kernel
@@ -632,16 +937,19 @@ __global__ __launch_bounds__(128) void quantize_vectors_kernel(QuantArgs a, uint
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t st) {
   const bool f16 = a.f16 && !(a.flags & kInputRotated);
   if (a.T >= 64) {
-    dim3 grid((a.T + 255) / 256, a.B * a.H, a.nlayers);
+    const int per_seq = (int)(((int64_t)a.T + kGroup - 1) / kGroup);
+    const int blocks = pack_blocks((int64_t)per_seq * a.B * a.H * a.nlayers);
+    const DivMagic div_seq = make_div_magic((uint32_t)per_seq), div_h = make_div_magic((uint32_t)a.H);
     const bool vq = (a.flags & kVQjl) != 0;
-    if (f16 && vq)
-      hipLaunchKernelGGL((quantize_tiles_kernel<true, true>), grid, dim3(256), 0, st, a);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kPackThreads), 0, st, a, blocks, per_seq, div_seq, div_h);
+    };
+    if (a.flags & kInputRotated)
+      vq ? launch(quantize_tiles_kernel<false, true, true>) : launch(quantize_tiles_kernel<false, false, true>);
     else if (f16)
-      hipLaunchKernelGGL((quantize_tiles_kernel<true, false>), grid, dim3(256), 0, st, a);
-    else if (vq)
-      hipLaunchKernelGGL((quantize_tiles_kernel<false, true>), grid, dim3(256), 0, st, a);
+      vq ? launch(quantize_tiles_kernel<true, true, false>) : launch(quantize_tiles_kernel<true, false, false>);
     else
-      hipLaunchKernelGGL((quantize_tiles_kernel<false, false>), grid, dim3(256), 0, st, a);
+      vq ? launch(quantize_tiles_kernel<false, true, false>) : launch(quantize_tiles_kernel<false, false, false>);
   } else {
     const uint32_t total = (uint32_t)((int64_t)a.nlayers * a.B * a.T * a.H);
     if (f16)

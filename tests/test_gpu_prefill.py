@@ -1,0 +1,122 @@
+"""The prefill kernel at the edges of its groups of 32 tokens, of its words and
+16-byte runs of slots, of its shares of (layer, head)s, of its windows of 64
+sequences, and at the scales where it stops leaving a vector's scale in.
+
+Against the oracle by the rule of assert_agree_up_to_threshold_rounding, and
+byte for byte against calls that reach the same tokens another way."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_26110_amd as tq
+from gpu_cases import Case, assert_agree_up_to_threshold_rounding, device_bytes
+from oracle import oracle
+from paper_2603_26110_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _planes(cache):
+    return cache.k_codes.clone(), cache.v_codes.clone(), cache.scalars.clone()
+
+
+@pytest.mark.parametrize("io", ["f16", "f32"])
+@pytest.mark.parametrize("T,first,flags", [
+    (64, 0, tq.V_ROTATE), (65, 5, tq.V_ROTATE), (95, 8, 0), (96, 32, tq.V_ROTATE | tq.ROPE_HALF),
+    (97, 37, tq.V_ROTATE | tq.V_QJL), (127, 24, tq.V_QJL), (161, 63, tq.V_ROTATE | tq.QJL_PAPER),
+    (72, 31, tq.V_ROTATE | tq.QJL_PAPER | tq.V_QJL),
+])
+def test_prefill_at_group_and_slot_edges(T, first, flags, io):
+    B, H = 2, 2
+    cap = (T + first + 127) // 64 * 64
+    case = Case(70 + T, 1, H, B, T, io=io, flags=flags, slots=B * cap, slot0=[first, cap + first], pos0=[0, 11])
+    cache = tq.Cache(1, H, B * cap)
+    for t in (cache.k_codes, cache.v_codes):
+        t.copy_(torch.randint(0, 256, t.shape, dtype=torch.uint8, device="cuda"))
+    before = device_bytes(cache)
+    oc = oracle.Cache(1, H, B * cap)
+    oc.k[:], oc.v[:] = before.k, before.v                    # (neighbouring slots keep their bits)
+    case.gpu_quantize(cache)
+    torch.cuda.synchronize()
+    case.oracle_quantize(oc)
+    got = device_bytes(cache)
+    assert_agree_up_to_threshold_rounding(case, got, oc, B, T, H, tokens=sorted({0, 1, 7, 31, 32, T - 2, T - 1}))
+    # all bytes of slots that were not written are as they were
+    written = np.zeros(B * cap, bool)
+    for b in range(B):
+        written[b * cap + first:b * cap + first + T] = True
+    tiles = lambda p: p.reshape(H, B * cap // 64, 2, 64, 16)
+    nib = lambda p: np.stack([tiles(p) & 15, tiles(p) >> 4], -1).reshape(H, B * cap // 64, 2, 64, 32)
+    v_got = nib(got.v).transpose(0, 1, 2, 4, 3).reshape(H, B * cap, 64)
+    v_old = nib(before.v).transpose(0, 1, 2, 4, 3).reshape(H, B * cap, 64)
+    np.testing.assert_array_equal(v_got[:, ~written], v_old[:, ~written])
+    k_of = lambda p: tiles(p).transpose(0, 1, 3, 2, 4).reshape(H, B * cap, 32)
+    np.testing.assert_array_equal(k_of(got.k)[:, ~written], k_of(before.k)[:, ~written])
+
+
+def test_ragged_windows_of_many_sequences():
+    # 150 sequences (three windows of 64), some empty, against each alone
+    g = synth.rng(77)
+    B, T, H = 150, 100, 2
+    lens = g.integers(0, T + 1, B)
+    lens[[0, 3, 63, 64, 127, 149]] = [0, T, 0, 33, 32, T]
+    cap = 128
+    case = Case(78, 1, H, B, T, slots=B * cap, slot0=[b * cap + b % 9 for b in range(B)], pos0=[b % 7 for b in range(B)])
+    args = (case.t("pi"), case.t("lut_k"), case.t("lut_v"), case.t("S"))
+    ragged, each = tq.Cache(1, H, B * cap), tq.Cache(1, H, B * cap)
+    tokens = torch.tensor(lens, dtype=torch.int32).cuda()
+    tq.quantize_pack(case.params(), ragged, case.t("k"), case.t("v"), case.t("pos0"), case.t("slot0"), *args,
+                     seq_tokens=tokens)
+    for b in range(B):
+        tq.quantize_pack(case.params(), each, case.t("k")[:, b:b + 1].contiguous(), case.t("v")[:, b:b + 1].contiguous(),
+                         case.t("pos0")[b:b + 1].clone(), case.t("slot0")[b:b + 1].clone(), *args,
+                         seq_tokens=tokens[b:b + 1].clone())
+    for x, y in zip(_planes(ragged), _planes(each)):
+        assert torch.equal(x, y)
+
+
+def test_shares_over_many_heads():
+    # 36 x 40 (layer, head)s of two groups: a block's share takes more than the
+    # four that it stages at once; one (layer, head) has a bad table
+    L, H, T = 36, 40, 64
+    case = Case(79, L, H, 1, T, slots=128)
+    case.lut_v[20, 7, 3] = case.lut_v[20, 7, 4]
+    args = lambda: (case.t("pi"), case.t("lut_k"), case.t("lut_v"), case.t("S"))
+    whole, each = tq.Cache(L, H, 128), tq.Cache(L, H, 128)
+    tq.quantize_pack(case.params(), whole, case.t("k"), case.t("v"), case.t("pos0"), case.t("slot0"), *args())
+    for l in range(L):
+        tq.quantize_pack(case.params(), each, case.t("k")[l:l + 1].contiguous(), case.t("v")[l:l + 1].contiguous(),
+                         case.t("pos0"), case.t("slot0"), *args(), layer0=l)
+    for x, y in zip(_planes(whole), _planes(each)):
+        assert torch.equal(x, y)
+    k = whole.k_codes.view(L, H, 128 * 32)
+    assert not k[20, 7].any() and all(bool(k[l, h].any()) for l, h in ((20, 6), (20, 8), (0, 0), (35, 39)))
+
+
+@pytest.mark.parametrize("e", [-60, -39, -20, 30, 41, 50])
+def test_codes_do_not_depend_on_a_power_of_two(e):
+    # RoPE, the rotation, norms and levels scale exactly while nothing leaves
+    # fp32's range: the same codes, signs and residual norms
+    case = Case(80, 1, 2, 1, 80, io="f32", flags=tq.V_ROTATE | tq.V_QJL, slots=128)
+    one, scaled = tq.Cache(1, 2, 128), tq.Cache(1, 2, 128)
+    case.gpu_quantize(one)
+    case.gpu_quantize(scaled, k=case.t("k") * 2.0 ** e, v=case.t("v") * 2.0 ** e)
+    assert torch.equal(one.k_codes, scaled.k_codes) and torch.equal(one.v_codes, scaled.v_codes)
+    assert torch.equal(one.scalars.view(-1, 4)[:, 1::2], scaled.scalars.view(-1, 4)[:, 1::2])
+
+
+def test_subnormal_fp16_values():
+    # fp16 values enter the products as they are; the fp32 path scales them first.
+    # Both are within rounding of x^, so codes differ only at thresholds (3e-6 of
+    # the coordinates against 64 bits elsewhere) and norms by an fp16 ulp.
+    case = Case(81, 1, 4, 1, 256, io="f16", flags=tq.V_ROTATE, slots=256)
+    g = synth.rng(82)
+    case.v = (g.integers(-255, 256, case.v.shape) * 2.0 ** -24).astype(np.float16)
+    half, full = tq.Cache(1, 4, 256), tq.Cache(1, 4, 256)
+    case.gpu_quantize(half)
+    p = case.params(io="f32")
+    tq.quantize_pack(p, full, case.t("k").float(), case.t("v").float(), case.t("pos0"), case.t("slot0"), case.t("pi"),
+                     case.t("lut_k"), case.t("lut_v"), case.t("S"))
+    assert float((half.v_codes != full.v_codes).float().mean()) <= 1e-4
+    n = [c.scalars.view(torch.float16).view(-1, 4)[:, 2].float() for c in (half, full)]
+    assert float((n[0] - n[1]).abs().max()) <= 2.0 ** -24 and float(n[0].min()) > 0
