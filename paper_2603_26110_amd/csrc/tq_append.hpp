@@ -13,6 +13,9 @@ namespace tq {
 // Write one dimension-major V nibble group: `mask` selects the nibbles of
 // `word` this writer owns. Whole words are stored; partial words are merged
 // with atomics so concurrent writers of neighbouring slots do not collide.
+// (The two atomics cost more than the rest of a short append: callers bring
+// as many slots of a word together as they can. A part of a word is never
+// stored plainly: a neighbour's 32-bit atomic may be in another XCD's L2.)
 __device__ __forceinline__ void store_v_word(uint32_t* addr, uint32_t word, uint32_t mask) {
   if (mask == 0xFFFFFFFFu) {
     *addr = word;
@@ -173,11 +176,36 @@ struct Appended {
   uint32_t scal;
 };
 
+// Key word bits of one quantized key (lane i: the nibble of dimension i) as
+// token-major key words (index bits 3j, sign bit 24 + j), stored into slot
+// `slot` of head lh with its [n_k, g_k]; lane 8w ends with word w.
+__device__ __forceinline__ uint32_t store_key(uint32_t nib, uint32_t scal, int64_t slot, int64_t lh, uint8_t* k_codes,
+                                              uint16_t* scalars, int64_t slots, int i) {
+  uint32_t word = key_code_bits(nib & 7u, nib >> 3, i & 7);
+  word |= __shfl_xor(word, 1, 64);
+  word |= __shfl_xor(word, 2, 64);
+  word |= __shfl_xor(word, 4, 64);
+  uint8_t* kreg = k_codes + lh * slots * 32;
+  if ((i & 7) == 0) {
+    const int w = i >> 3;
+    *reinterpret_cast<uint32_t*>(kreg + tile_half_offset(slot >> 6, w >> 2, (int)(slot & 63)) + (w & 3) * 4) = word;
+  }
+  if (i == 0) reinterpret_cast<uint32_t*>(scalars + (lh * slots + slot) * 4)[0] = scal;
+  return word;
+}
+
+// Nibbles of dimension i (lane i) for some of the eight slots 8G .. 8G + 7 of
+// head lh (`mask`: theirs).
+__device__ __forceinline__ void store_value_nibbles(uint32_t word, uint32_t mask, int64_t G, int64_t lh,
+                                                    uint8_t* v_codes, int64_t slots, int i) {
+  uint8_t* vreg = v_codes + lh * slots * 32;
+  store_v_word(reinterpret_cast<uint32_t*>(vreg + tile_half_offset(G >> 3, (int)(G & 7) >> 2, i) + (G & 3) * 4), word,
+               mask);
+}
+
 // Rotate (when `rotate`), quantize and store one vector into slot `slot` of
-// head lh: keys as token-major key words plus [n_k, g_k], values as
-// dimension-major nibbles plus [n_v, g_v]. Pi and S are staged in LDS in
-// layout LY; xs and rs are this wave's two 64-float staging vectors; NB as in
-// row_dot.
+// head lh. Pi and S are staged in LDS in layout LY; xs and rs are this wave's
+// two 64-float staging vectors; NB as in row_dot.
 template <class LY, int NB = 16>
 __device__ __forceinline__ Appended append_wave(float x, bool is_v, bool rotate, const Levels& L,
                                                 const float* pi, const float* s, float* xs, float* rs,
@@ -192,28 +220,9 @@ __device__ __forceinline__ Appended append_wave(float x, bool is_v, bool rotate,
   uint32_t n16, g16;
   const uint32_t nib = quantize_wave<LY, NB>(x, L, s, sign_mode, xs, rs, i, &n16, &g16);
   const uint32_t scal = n16 | (g16 << 16);
-  const int64_t tile = slot >> 6;
-  const int r = (int)(slot & 63);
-  if (!is_v) {
-    // key: token-major key words (index bits 3j, sign bit 24 + j); lane 8w
-    // ends with word w
-    uint32_t word = key_code_bits(nib & 7u, nib >> 3, i & 7);
-    word |= __shfl_xor(word, 1, 64);
-    word |= __shfl_xor(word, 2, 64);
-    word |= __shfl_xor(word, 4, 64);
-    uint8_t* kreg = k_codes + lh * slots * 32;
-    if ((i & 7) == 0) {
-      const int w = i >> 3;
-      *reinterpret_cast<uint32_t*>(kreg + tile_half_offset(tile, w >> 2, r) + (w & 3) * 4) = word;
-    }
-    if (i == 0) reinterpret_cast<uint32_t*>(scalars + (lh * slots + slot) * 4)[0] = scal;
-    return Appended{word, scal};
-  }
-  // value: dimension-major, one nibble of dimension i's word for this slot
-  uint8_t* vreg = v_codes + lh * slots * 32;
-  const int cc = r >> 5, G4 = (r & 31) >> 3, jj = r & 7;
-  uint32_t* addr = reinterpret_cast<uint32_t*>(vreg + tile_half_offset(tile, cc, i) + G4 * 4);
-  store_v_word(addr, nib << (4 * jj), 15u << (4 * jj));
+  if (!is_v) return Appended{store_key(nib, scal, slot, lh, k_codes, scalars, slots, i), scal};
+  const int sh = 4 * (int)(slot & 7);
+  store_value_nibbles(nib << sh, 15u << sh, slot >> 3, lh, v_codes, slots, i);
   if (i == 0) reinterpret_cast<uint32_t*>(scalars + (lh * slots + slot) * 4)[1] = scal;
   return Appended{nib, scal};
 }

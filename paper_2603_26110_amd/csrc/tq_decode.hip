@@ -190,42 +190,11 @@ __device__ __forceinline__ void key_word_score(const float* ta, const float* tb,
 
 
 
-// Token weights of a 64-token tile for the lane-per-dimension value loop.
-// Lane t holds w_t; two lane swaps give four registers R_j holding tokens
-// 16j .. 16j+15 in every 16-lane row (v_permlane32_swap exchanges the upper
-// half of one register with the lower half of another, v_permlane16_swap the
-// odd rows of one with the even rows of another). An FMA then reads w_{16j+k}
-// through a DPP row broadcast of lane k (row_newbcast), so no weight costs an
-// instruction of its own.
-struct TileWeights {
-  float r[4];
-};
-
-__device__ __forceinline__ TileWeights spread_weights(float w) {
-  const int wi = __float_as_int(w);
-  const auto h = __builtin_amdgcn_permlane32_swap(wi, wi, false, false);   // rows 0 1 0 1 | 2 3 2 3
-  const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);   // 0 0 0 0 | 1 1 1 1
-  const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);   // 2 2 2 2 | 3 3 3 3
-  TileWeights tw;
-  tw.r[0] = __int_as_float(lo[0]);
-  tw.r[1] = __int_as_float(lo[1]);
-  tw.r[2] = __int_as_float(hi[0]);
-  tw.r[3] = __int_as_float(hi[1]);
-  return tw;
-}
-
-// acc += w_{16j+K} * c, the weight taken from register R_j by a row broadcast.
-template <int K>
-__device__ __forceinline__ void fma_row_bcast(float& acc, float rj, float c) {
-  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc) : "v"(rj), "v"(c), "i"(K));
-}
-
 // The 16 tokens 8*W8 .. 8*W8+15 of two value words: acc_{jj & 3} += w_t c_V[code].
 // The 16 table reads are issued together (the empty asm makes them complete
 // before the first FMA), so the LDS latency is paid once per word pair.
 template <int W8>
-__device__ __forceinline__ void value_words(const TileWeights& tw, uint32_t x0, uint32_t x1,
+__device__ __forceinline__ void value_words(const LaneSpread& tw, uint32_t x0, uint32_t x1,
                                             const char* vtab, float& o0, float& o1, float& o2,
                                             float& o3) {
   uint32_t off[16];
@@ -259,7 +228,7 @@ __device__ __forceinline__ void value_words(const TileWeights& tw, uint32_t x0, 
 
 // The V residual term of one word: acc += sum_t (+-1 by the sign bit) g_t.
 template <int W8>
-__device__ __forceinline__ void value_sign_word(const TileWeights& tg, uint32_t x, float& acc) {
+__device__ __forceinline__ void value_sign_word(const LaneSpread& tg, uint32_t x, float& acc) {
   constexpr int J = W8 / 2, K0 = 8 * (W8 & 1);
   const float rj = tg.r[J];
   float sgn[8];
@@ -691,15 +660,15 @@ void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
       const float wg = VQJL ? (paper ? wv : wv * gv) : 0.0f;
 
       // ---- value accumulate, one lane per dimension; token weights through
-      // row broadcasts (spread_weights)
+      // row broadcasts (spread_lanes)
       const uint32_t vw[8] = {cur.v0.x, cur.v0.y, cur.v0.z, cur.v0.w, cur.v1.x, cur.v1.y, cur.v1.z, cur.v1.w};
-      const TileWeights tw = spread_weights(wv);
+      const LaneSpread tw = spread_lanes(wv);
       value_words<0>(tw, vw[0], vw[1], vtab, o0, o1, o2, o3);
       value_words<2>(tw, vw[2], vw[3], vtab, o0, o1, o2, o3);
       value_words<4>(tw, vw[4], vw[5], vtab, o0, o1, o2, o3);
       value_words<6>(tw, vw[6], vw[7], vtab, o0, o1, o2, o3);
       if (VQJL) {
-        const TileWeights tg = spread_weights(wg);
+        const LaneSpread tg = spread_lanes(wg);
         value_sign_word<0>(tg, vw[0], sg);
         value_sign_word<1>(tg, vw[1], sg);
         value_sign_word<2>(tg, vw[2], sg);

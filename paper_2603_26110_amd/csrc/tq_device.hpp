@@ -224,6 +224,39 @@ __device__ __forceinline__ QuantOut quantize_lane(float (&xh)[kDim], float scale
   return o;
 }
 
+// The 64 lanes' values of a wave, for sums that every lane forms over all of
+// them (decode: a tile's token weights; appends: a vector's elements). Lane t
+// holds w_t; two lane swaps give four registers R_j holding lanes
+// 16j .. 16j+15 in every 16-lane row (v_permlane32_swap exchanges the upper
+// half of one register with the lower half of another, v_permlane16_swap the
+// odd rows of one with the even rows of another). An FMA then reads w_{16j+k}
+// through a DPP row broadcast of lane k (row_newbcast), so no value costs an
+// instruction of its own. (A DPP read needs two wait states after the vector
+// instruction that wrote the register, which the compiler does not see here.)
+struct LaneSpread {
+  float r[4];
+};
+
+__device__ __forceinline__ LaneSpread spread_lanes(float w) {
+  const int wi = __float_as_int(w);
+  const auto h = __builtin_amdgcn_permlane32_swap(wi, wi, false, false);   // rows 0 1 0 1 | 2 3 2 3
+  const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);   // 0 0 0 0 | 1 1 1 1
+  const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);   // 2 2 2 2 | 3 3 3 3
+  LaneSpread tw;
+  tw.r[0] = __int_as_float(lo[0]);
+  tw.r[1] = __int_as_float(lo[1]);
+  tw.r[2] = __int_as_float(hi[0]);
+  tw.r[3] = __int_as_float(hi[1]);
+  return tw;
+}
+
+// acc += w_{16j+K} * c, the weight taken from register R_j by a row broadcast.
+template <int K>
+__device__ __forceinline__ void fma_row_bcast(float& acc, float rj, float c) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "+v"(acc) : "v"(rj), "v"(c), "i"(K));
+}
+
 // Wave-wide reductions (64 lanes).
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

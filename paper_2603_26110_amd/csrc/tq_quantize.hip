@@ -2,22 +2,26 @@
 // table codes -> residual -> QJL sign bits -> packed cache (TurboESM Sec. 3.1
 // prefill steps 1, 3, 4; Sec. 3.3; Sec. 3.4; Sec. 4.2).
 //
-// Two kernels:
+// Three kernels:
 //   quantize_tiles_kernel   for prefill-sized T: the keys and values of 32
 //                           tokens per wave; the rotations x^ = Pi x' of
 //                           these 64 vectors and the projections S r run on
 //                           the matrix cores (fp16 MFMA on hi/lo parts), one
 //                           lane per vector runs the quantizer steps.
+//   quantize_batch_kernel   many short sequences: a wave takes four vectors at a
+//                           time, one lane per dimension, and a block's waves
+//                           share the staged Pi and S.
 //   quantize_vectors_kernel one wave per vector (one lane per dimension; the
 //                           key and the value of a token-head in parallel), for
 //                           decode-step appends with small T; its rotation is
 //                           an fma chain over k ascending.
-// Both run the quantizer steps (norm, levels, residual, projected signs) in
+// All run the quantizer steps (norm, levels, residual, projected signs) in
 // the fixed binary32 order of quantize_lane / quantize_wave, so identical x^
-// give identical bits; for raw inputs the two rotations sum in different
-// orders, so a code can differ where x^ sits within rounding of a threshold.
+// give identical bits; for raw inputs the prefill's rotation sums in another
+// order than the other two's, so a code can differ where x^ sits within rounding of a threshold.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "tq_append.hpp"
 #include "tq_device.hpp"
@@ -934,6 +938,239 @@ __global__ __launch_bounds__(128) void quantize_vectors_kernel(QuantArgs a, uint
                        a.k_codes, a.v_codes, a.scalars, a.slots, i);
 }
 
+// ------------------------------------------- wave-per-four-vectors kernel
+// Rows lie 68 floats apart, so that the reads of four rows at one column do
+// not meet in a bank.
+constexpr int kVecPitch = kDim + 4;
+
+constexpr int kRowChunks = 8;       // 16-byte chunks of a row in registers at a time
+
+// Row i of a 64 x 64 matrix staged in `m` (Swz16) times NT vectors held one
+// element per lane: fma chains over k ascending (row_dot's). The row is read
+// once for all of them, and their elements reach the chains through row
+// broadcasts: reading them from LDS too (one 16-byte broadcast per four
+// elements and vector) made its return path the bound.
+template <int K0, int NT, int... K4>
+__device__ __forceinline__ void row_dots_steps(const float4 (&mr)[kRowChunks], const LaneSpread (&v)[NT],
+                                               float (&acc)[NT], std::integer_sequence<int, K4...>) {
+  auto step = [&](auto k4, const float4& m) {
+    constexpr int K = 4 * (K0 + k4.value), J = K / 16;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fma_row_bcast<K % 16>(acc[t], v[t].r[J], m.x);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fma_row_bcast<K % 16 + 1>(acc[t], v[t].r[J], m.y);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fma_row_bcast<K % 16 + 2>(acc[t], v[t].r[J], m.z);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fma_row_bcast<K % 16 + 3>(acc[t], v[t].r[J], m.w);
+  };
+  (step(std::integral_constant<int, K4>{}, mr[K4]), ...);
+}
+
+template <int NT>
+__device__ __forceinline__ void row_dots(const float* m, int i, float (&x)[NT]) {
+  const float4* m4 = reinterpret_cast<const float4*>(m);
+  float4 mr[kRowChunks];
+#pragma unroll
+  for (int k4 = 0; k4 < kRowChunks; ++k4) mr[k4] = m4[Swz16::chunk(i, k4)];
+  LaneSpread v[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    v[t] = spread_lanes(x[t]);
+    x[t] = 0.0f;
+  }
+  // (the two wait states before a DPP read)
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    asm volatile("s_nop 1" : "+v"(v[t].r[0]), "+v"(v[t].r[1]), "+v"(v[t].r[2]), "+v"(v[t].r[3]));
+  constexpr auto steps = std::make_integer_sequence<int, kRowChunks>{};
+  row_dots_steps<0>(mr, v, x, steps);
+#pragma unroll
+  for (int k4 = 0; k4 < kRowChunks; ++k4) mr[k4] = m4[Swz16::chunk(i, kRowChunks + k4) + after(x[0])];
+  row_dots_steps<kRowChunks>(mr, v, x, steps);
+}
+
+// A block stages Pi and S of one (layer, head) once (direct 16-byte copies
+// into LDS) for a chunk of its tokens, the sequences' tokens counted through;
+// waves 0 .. 3 take their keys and waves 4 .. 7 their values, four at a time
+// (one lane per dimension). The steps of each vector are append_wave's, in its
+// order, so the bytes are quantize_vectors_kernel's; four vectors share the
+// reads of the matrix rows, and their norm chains run in different lanes (lane
+// t runs vector t's).
+//
+// What bounds it: the fma chains and the waits between them, at four waves per
+// SIMD. fp16, 60 tokens x 1440 (layer, head)s 115 us, 8 tokens of 64 sequences
+// x 20 heads 23.5 us; 324 and 39.1 us in quantize_vectors_kernel, whose blocks
+// stage 32 KB per token and merge every value nibble by two atomics of its own
+// (alone 65 of the 180 us that this kernel took with them).
+constexpr int kVecWaves = 8;
+constexpr int kVecTokens = 4;       // per wave
+
+template <bool F16>
+__global__ __launch_bounds__(kVecWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
+void quantize_batch_kernel(QuantArgs a, int total_blocks, int per_xcd, int chunk_tokens, DivMagic div_chunks,
+                           DivMagic div_t, DivMagic div_h, int chunks) {
+  constexpr int NT = kVecTokens;
+  __shared__ __attribute__((aligned(16))) float s_pi[kDim * kDim];   // Swz16
+  __shared__ __attribute__((aligned(16))) float s_s[kDim * kDim];
+  __shared__ __attribute__((aligned(16))) float s_x[kVecWaves][NT * kVecPitch];
+  const int work = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+  if (work >= total_blocks) return;
+  const int head = (int)div_magic(work, div_chunks);     // nlayers x H, relative to layer0
+  const int chunk = work - head * chunks;
+  const int li = (int)div_magic(head, div_h), h = head - li * a.H;
+  const int64_t lh = (int64_t)a.layer0 * a.H + head;
+  const int i = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool is_v = wave >= kVecWaves / 2;
+  const bool rotated = (a.flags & kInputRotated) != 0;
+  const bool paper = (a.flags & kQjlPaper) != 0;
+  const int ksign = paper ? 2 : 1;
+  const int sign_mode = is_v ? ((a.flags & kVQjl) ? ksign : 0) : ksign;
+  const bool rotate = !rotated && (!is_v || (a.flags & kVRotate));
+  const bool half = (a.flags & kRopeHalf) != 0;
+  {
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    const float* pig = a.pi + lh * kDim * kDim;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c0 = (wave + kVecWaves * j) * 64;
+      if (!rotated)                                      // keys rotate unless pre-rotated
+        __builtin_amdgcn_global_load_lds(pig + Swz16::source(c0 + i) * 4, (lds_ptr)(s_pi + c0 * 4), 16, 0, 0);
+      if (!paper)                                        // keys use the projection unless paper
+        __builtin_amdgcn_global_load_lds(a.qjl_s + Swz16::source(c0 + i) * 4, (lds_ptr)(s_s + c0 * 4), 16, 0, 0);
+    }
+  }
+  const int all = a.B * a.T;
+  const int stop = min(all, (chunk + 1) * chunk_tokens);
+  // Four tokens from n0 on: written or not, their slots, and the lane's element
+  // and RoPE (cos, sin) of each. Loaded ahead: the first ones with the staging,
+  // the next ones while the ones before are quantized.
+  float x_in[NT];
+  float2 cs[NT];
+  int64_t slot_in[NT];
+  uint32_t ok_in = 0;
+  auto fetch = [&](int n0) {
+    ok_in = 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int n = min(n0 + t, all - 1);
+      const int b = (int)div_magic(n, div_t), j = n - b * a.T;
+      const int Tb = a.tokens ? min(max(scalar_load(a.tokens + b), 0), a.T) : a.T;
+      const int pos = scalar_load(a.pos0 + b) + j;
+      const int64_t slot = scalar_load(a.slot0 + b) + j;
+      slot_in[t] = slot;
+      x_in[t] = 0.0f;
+      cs[t] = make_float2(1.0f, 0.0f);
+      if (n0 + t < stop && j < Tb && slot >= 0 && slot < a.slots &&
+          (rotated || (pos >= 0 && pos < a.rope_positions))) {
+        ok_in |= 1u << t;
+        const int64_t row = ((((int64_t)li * a.B + b) * a.T + j) * a.H + h) * kDim;
+        x_in[t] = load_in(is_v ? a.v : a.k, row + i, F16);
+        if (!is_v && !rotated)
+          cs[t] = reinterpret_cast<const float2*>(a.rope_cs + (int64_t)pos * 2 * kPairs)[half ? (i & 31) : (i >> 1)];
+      }
+    }
+  };
+  int n0 = chunk * chunk_tokens + (wave & 3) * NT;
+  fetch(n0);
+  const Levels L = load_levels((is_v ? a.lut_v : a.lut_k) + lh * 8);
+  const Levels Lo = load_levels((is_v ? a.lut_k : a.lut_v) + lh * 8);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  // a (layer, head) whose K or V table is not strictly ascending is not written
+  if (!levels_ascending(L) || !levels_ascending(Lo)) return;
+
+  float* xs = s_x[wave];
+  const float* own = xs + (i & (NT - 1)) * kVecPitch;
+  for (; n0 < stop; n0 += 4 * NT) {
+    float x[NT];
+    int64_t slot[NT];
+    const uint32_t ok = ok_in;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      x[t] = !is_v && !rotated ? rope_wave(x_in[t], cs[t], half, i) : x_in[t];
+      slot[t] = slot_in[t];
+    }
+    fetch(n0 + 4 * NT);
+    // ---- rotation
+    if (rotate) row_dots<NT>(s_pi, i, x);
+    // ---- norm, levels, residual
+#pragma unroll
+    for (int t = 0; t < NT; ++t) xs[t * kVecPitch + i] = x[t];
+    wave_sync_lds();
+    const float n_own = sqrtf(sum_squares<8>(own));
+    const float inv_own = (n_own == 0.0f) ? 0.0f : 8.0f / n_own;
+    wave_sync_lds();
+    TQ_PIN_LEVELS(L);
+    uint32_t nib[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float u = x[t] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv_own), t));
+      const float lv = nearest_level(u, TQ_LEVELS(L), &nib[t]);
+      x[t] = u - lv;
+      xs[t * kVecPitch + i] = x[t];
+    }
+    wave_sync_lds();
+    const float g_own = sqrtf(sum_squares<8>(own));
+    const uint32_t scal_own = store_norm(n_own) | ((sign_mode == 0 ? 0u : store_norm(g_own)) << 16);
+    // ---- signs
+    if (sign_mode == 1) {
+      row_dots<NT>(s_s, i, x);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) nib[t] |= ((x[t] < 0.0f) ? 0u : 1u) << 3;
+    } else if (sign_mode == 2) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) nib[t] |= ((x[t] < 0.0f) ? 0u : 1u) << 3;
+    }
+    wave_sync_lds();                                     // xs is written again by the next tokens
+    // ---- stores; values of tokens in the same eight slots together
+    if (!is_v) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if (ok & (1u << t))
+          store_key(nib[t], (uint32_t)__builtin_amdgcn_readlane((int)scal_own, t), slot[t], lh, a.k_codes, a.scalars,
+                    a.slots, i);
+    } else {
+      uint32_t word = 0, mask = 0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (!(ok & (1u << t))) continue;
+        const int sh = 4 * (int)(slot[t] & 7);
+        word |= nib[t] << sh;
+        mask |= 15u << sh;
+        const int u = t + 1 < NT ? t + 1 : t;
+        if (u == t || !(ok & (1u << u)) || (slot[u] >> 3) != (slot[t] >> 3)) {
+          store_value_nibbles(word, mask, slot[t] >> 3, lh, a.v_codes, a.slots, i);
+          word = 0;
+          mask = 0;
+        }
+      }
+      if (i < NT && (ok & (1u << i))) {
+        int64_t s = slot[0];
+#pragma unroll
+        for (int t = 1; t < NT; ++t) s = i == t ? slot[t] : s;
+        reinterpret_cast<uint32_t*>(a.scalars + (lh * a.slots + s) * 4)[1] = scal_own;
+      }
+    }
+  }
+}
+
+// quantize_batch_kernel takes a call of short sequences from this many tokens
+// per (layer, head), and token-heads in all, on. One token each (fp16, us, this
+// kernel / quantize_vectors_kernel): 64 tokens x 20 heads 10.4 / 8.6, 12 x 180
+// 11.5 / 13.0, 4 x 1440 27.7 / 24.5, 8 x 660 23.8 / 22.9, 8 x 1440 39 / 43.
+constexpr int64_t kBatchTokenHeads = 2048, kBatchTokens = 12;
+
+// Its tokens per block: a pass takes 16 of a (layer, head); as many passes as
+// bring the blocks down to the two per compute unit that run at once (a pass
+// more costs less than a second staging).
+static int batch_chunk(int64_t heads, int64_t tokens) {
+  const int64_t passes = (tokens + 15) / 16;
+  const int64_t per_head = std::max<int64_t>(1, std::min(passes, 2 * (int64_t)kComputeUnits / heads));
+  return (int)((passes + per_head - 1) / per_head * 16);
+}
+
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t st) {
   const bool f16 = a.f16 && !(a.flags & kInputRotated);
   if (a.T >= 64) {
@@ -951,7 +1188,20 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t st) {
     else
       vq ? launch(quantize_tiles_kernel<false, true, false>) : launch(quantize_tiles_kernel<false, false, false>);
   } else {
-    const uint32_t total = (uint32_t)((int64_t)a.nlayers * a.B * a.T * a.H);
+    const int64_t heads = (int64_t)a.nlayers * a.H, tokens = (int64_t)a.B * a.T;
+    const uint32_t total = (uint32_t)(heads * tokens);
+    if (total >= kBatchTokenHeads && tokens >= kBatchTokens) {
+      const int chunk = batch_chunk(heads, tokens);
+      const int chunks = (int)((tokens + chunk - 1) / chunk), blocks = (int)(heads * chunks);
+      const int per_xcd = (blocks + kXcds - 1) / kXcds;
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)per_xcd * kXcds), dim3(kVecWaves * 64), 0, st, a, blocks, per_xcd,
+                           chunk, make_div_magic((uint32_t)chunks), make_div_magic((uint32_t)a.T),
+                           make_div_magic((uint32_t)a.H), chunks);
+      };
+      f16 ? launch(quantize_batch_kernel<true>) : launch(quantize_batch_kernel<false>);
+      return hipGetLastError();
+    }
     if (f16)
       hipLaunchKernelGGL(quantize_vectors_kernel<true>, dim3(total), dim3(128), 0, st, a, total);
     else

@@ -120,3 +120,34 @@ def test_subnormal_fp16_values():
     assert float((half.v_codes != full.v_codes).float().mean()) <= 1e-4
     n = [c.scalars.view(torch.float16).view(-1, 4)[:, 2].float() for c in (half, full)]
     assert float((n[0] - n[1]).abs().max()) <= 2.0 ** -24 and float(n[0].min()) > 0
+
+
+@pytest.mark.parametrize("io", ["f16", "f32"])
+@pytest.mark.parametrize("T,lens,flags", [
+    (1, None, tq.V_ROTATE), (7, None, tq.V_ROTATE), (13, None, tq.V_QJL), (63, None, tq.V_ROTATE | tq.V_QJL),
+    (30, [30, 0, 1, 17, 29, 4, 8, 30], tq.V_ROTATE | tq.ROPE_HALF), (20, None, tq.V_ROTATE | tq.QJL_PAPER),
+])
+def test_short_sequences_in_a_batch_equal_each_alone(T, lens, flags, io):
+    # a batch large enough for the kernel that shares a block's Pi and S, against
+    # calls that the kernel of one vector per wave takes: the same bytes, and the
+    # neighbouring slots untouched (first slots at every remainder of 8)
+    H, B = 40, 64 if T == 1 else 8
+    cap = 128
+    slot0 = [b * cap + (3 * b) % 64 for b in range(B)]
+    slot0[B - 1] = B * cap - 1                               # its later tokens have no slot
+    case = Case(83 + T, 1, H, B, T, io=io, flags=flags, slots=B * cap, slot0=slot0, pos0=[5 * b for b in range(B)],
+                positions=5 * B - 2)                          # and the last position is past the table
+    args = (case.t("pi"), case.t("lut_k"), case.t("lut_v"), case.t("S"))
+    tokens = None if lens is None else torch.tensor(lens, dtype=torch.int32).cuda()
+    batch, each = tq.Cache(1, H, B * cap), tq.Cache(1, H, B * cap)
+    for x, y in zip((batch.k_codes, batch.v_codes), (each.k_codes, each.v_codes)):
+        x.copy_(torch.randint(0, 256, x.shape, dtype=torch.uint8, device="cuda"))
+        y.copy_(x)
+    tq.quantize_pack(case.params(), batch, case.t("k"), case.t("v"), case.t("pos0"), case.t("slot0"), *args,
+                     seq_tokens=tokens)
+    for b in range(B):
+        tq.quantize_pack(case.params(), each, case.t("k")[:, b:b + 1].contiguous(), case.t("v")[:, b:b + 1].contiguous(),
+                         case.t("pos0")[b:b + 1].clone(), case.t("slot0")[b:b + 1].clone(), *args,
+                         seq_tokens=None if lens is None else tokens[b:b + 1].clone())
+    for x, y in zip(_planes(batch), _planes(each)):
+        assert torch.equal(x, y)
