@@ -108,12 +108,23 @@ def _check(status: int) -> None:
         raise TQError(f"status {status}: {last_error()}")
 
 
+# A call's marshalling is a good part of a small launch's time (17 us of host
+# work per decode_step against 9 us of kernel, before): pointers go to ctypes as
+# plain integers, the current stream comes as its raw handle without a
+# torch.cuda.Stream object (0.1 us instead of 2), structures are built once per
+# call, and the checks of a call's tensors are one expression. Only where that
+# fails do the checks run one by one, in order, to raise.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else \
+    (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+def _stream(device) -> int:
+    """Handle of the current stream of a tensor's device."""
+    return _raw_stream(device.index)
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None) -> torch.Tensor:
@@ -179,31 +190,44 @@ def quantize_pack(params: Params, cache: Cache, k, v, pos0, slot0, pi, lut_k, lu
     ragged batch (tq_quantize_pack_ragged); rows beyond it are padding."""
     L = _load()
     want = torch.float32 if params.flags & INPUT_ROTATED else params.io_dtype
-    _dev(k, "k", want)
-    _dev(v, "v", want)
-    if k.dim() != 5 or k.shape[-1] != 64 or k.shape != v.shape or k.shape[3] != params.num_heads:
-        raise ValueError("k and v must be [nlayers][B][T][H][64] with matching shapes")
-    nl, B, T = k.shape[:3]
-    _dev(pos0, "pos0", torch.int32)
-    _dev(slot0, "slot0", torch.int64)
-    if pos0.numel() < B or slot0.numel() < B:
-        raise ValueError("pos0 and slot0 need B entries")
-    for name, t in (("pi", pi), ("lut_k", lut_k), ("lut_v", lut_v), ("qjl_s", qjl_s)):
-        _dev(t, name, torch.float32)
+    shape = k.shape if isinstance(k, torch.Tensor) else ()
+    try:
+        fine = (k.is_cuda and v.is_cuda and pos0.is_cuda and slot0.is_cuda and pi.is_cuda and lut_k.is_cuda
+                and lut_v.is_cuda and qjl_s.is_cuda and k.dtype is want and v.dtype is want
+                and pos0.dtype is torch.int32 and slot0.dtype is torch.int64 and pi.dtype is torch.float32
+                and lut_k.dtype is torch.float32 and lut_v.dtype is torch.float32 and qjl_s.dtype is torch.float32
+                and k.is_contiguous() and v.is_contiguous() and pos0.is_contiguous() and slot0.is_contiguous()
+                and pi.is_contiguous() and lut_k.is_contiguous() and lut_v.is_contiguous() and qjl_s.is_contiguous()
+                and len(shape) == 5 and shape[4] == 64 and shape == v.shape and shape[3] == params.num_heads
+                and pos0.numel() >= shape[1] and slot0.numel() >= shape[1])
+    except AttributeError:
+        fine = False
+    if not fine:
+        _dev(k, "k", want)
+        _dev(v, "v", want)
+        if k.dim() != 5 or k.shape[-1] != 64 or k.shape != v.shape or k.shape[3] != params.num_heads:
+            raise ValueError("k and v must be [nlayers][B][T][H][64] with matching shapes")
+        _dev(pos0, "pos0", torch.int32)
+        _dev(slot0, "slot0", torch.int64)
+        if pos0.numel() < k.shape[1] or slot0.numel() < k.shape[1]:
+            raise ValueError("pos0 and slot0 need B entries")
+        for name, t in (("pi", pi), ("lut_k", lut_k), ("lut_v", lut_v), ("qjl_s", qjl_s)):
+            _dev(t, name, torch.float32)
+    nl, B, T = shape[:3]
     p = params.c()
     c = cache.c()
     if seq_tokens is not None:
         _dev(seq_tokens, "seq_tokens", torch.int32)
         if seq_tokens.numel() < B:
             raise ValueError("seq_tokens needs B entries")
-        _check(L.tq_quantize_pack_ragged(ctypes.byref(p), ctypes.byref(c), _ptr(k), _ptr(v), B, T,
-                                         _ptr(seq_tokens), layer0, nl, _ptr(pos0), _ptr(slot0), _ptr(pi),
-                                         _ptr(lut_k), _ptr(lut_v), _ptr(qjl_s), _ptr(ebar),
-                                         _stream(k.device)))
+        _check(L.tq_quantize_pack_ragged(ctypes.byref(p), ctypes.byref(c), k.data_ptr(), v.data_ptr(), B, T,
+                                         seq_tokens.data_ptr(), layer0, nl, pos0.data_ptr(), slot0.data_ptr(),
+                                         pi.data_ptr(), lut_k.data_ptr(), lut_v.data_ptr(), qjl_s.data_ptr(),
+                                         _ptr(ebar), _stream(k.device)))
         return
-    _check(L.tq_quantize_pack(ctypes.byref(p), ctypes.byref(c), _ptr(k), _ptr(v), B, T, layer0, nl,
-                              _ptr(pos0), _ptr(slot0), _ptr(pi), _ptr(lut_k), _ptr(lut_v),
-                              _ptr(qjl_s), _ptr(ebar), _stream(k.device)))
+    _check(L.tq_quantize_pack(ctypes.byref(p), ctypes.byref(c), k.data_ptr(), v.data_ptr(), B, T, layer0, nl,
+                              pos0.data_ptr(), slot0.data_ptr(), pi.data_ptr(), lut_k.data_ptr(), lut_v.data_ptr(),
+                              qjl_s.data_ptr(), _ptr(ebar), _stream(k.device)))
 
 
 def decode_workspace_bytes(params: Params, B: int, nlayers: int, max_len: int) -> int:
@@ -211,37 +235,75 @@ def decode_workspace_bytes(params: Params, B: int, nlayers: int, max_len: int) -
     return int(_load().tq_decode_workspace_bytes(ctypes.byref(p), B, nlayers, max_len))
 
 
+def _decode_checks(params: Params, q, kv, positions, name, seq_slot0, seq_len, pi, lut_k, lut_v, qjl_s, ebar):
+    """The checks that the decode entry points share (kv: a step's (k, v), or ()). Returns q's shape."""
+    io = params.io_dtype
+    shape = q.shape if isinstance(q, torch.Tensor) else ()
+    try:
+        fine = (q.is_cuda and positions.is_cuda and seq_slot0.is_cuda and seq_len.is_cuda and pi.is_cuda
+                and lut_k.is_cuda and lut_v.is_cuda and qjl_s.is_cuda and q.dtype is io
+                and positions.dtype is torch.int32 and seq_slot0.dtype is torch.int64 and seq_len.dtype is torch.int32
+                and pi.dtype is torch.float32 and lut_k.dtype is torch.float32 and lut_v.dtype is torch.float32
+                and qjl_s.dtype is torch.float32 and q.is_contiguous() and positions.is_contiguous()
+                and seq_slot0.is_contiguous() and seq_len.is_contiguous() and pi.is_contiguous()
+                and lut_k.is_contiguous() and lut_v.is_contiguous() and qjl_s.is_contiguous()
+                and len(shape) == 4 and shape[3] == 64 and shape[2] == params.num_heads
+                and (ebar is None or (ebar.is_cuda and ebar.dtype is torch.float32 and ebar.is_contiguous())))
+        for t in kv:
+            fine = fine and t.is_cuda and t.dtype is io and t.is_contiguous() and t.shape == shape
+    except AttributeError:
+        fine = False
+    if not fine:
+        for n, t in zip("qkv", (q, *kv)):
+            _dev(t, n, io)
+        if q.dim() != 4 or q.shape[-1] != 64 or q.shape[2] != params.num_heads:
+            raise ValueError("q must be [nlayers][B][H][64]")
+        for t in kv:
+            if t.shape != q.shape:
+                raise ValueError("k and v must have the shape of q")
+        _dev(positions, name, torch.int32)
+        _dev(seq_slot0, "seq_slot0", torch.int64)
+        _dev(seq_len, "seq_len", torch.int32)
+        for n, t in (("pi", pi), ("lut_k", lut_k), ("lut_v", lut_v), ("qjl_s", qjl_s)):
+            _dev(t, n, torch.float32)
+        if ebar is not None:
+            _dev(ebar, "ebar", torch.float32)
+    return shape
+
+
+def _decode_out(params: Params, q, out):
+    """The output tensor: `out` checked, or a new one."""
+    dtype = torch.float32 if (params.flags & OUT_FP32 or params.io_dtype == torch.float32) else torch.float16
+    if out is None:
+        return torch.empty_like(q, dtype=dtype, memory_format=torch.contiguous_format)
+    return _dev(out, "out", dtype)
+
+
+def _decode_workspace(lib, p, B, nl, max_len, workspace, device):
+    """The workspace (`workspace` where it is large enough, or a new zeroed one) and its bytes."""
+    need = lib.tq_decode_workspace_bytes(p, B, nl, max_len)
+    size = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    if need > size:
+        workspace = torch.zeros(need, dtype=torch.uint8, device=device)
+        size = need
+    return workspace, size
+
+
 def decode_attend(params: Params, cache: Cache, q, q_pos, seq_slot0, seq_len, max_len: int,
                   pi, lut_k, lut_v, qjl_s, ebar=None, layer0: int = 0, out=None,
                   workspace=None) -> torch.Tensor:
     """q: [nlayers][B][H][64]. Returns out [nlayers][B][H][64]."""
     L = _load()
-    _dev(q, "q", params.io_dtype)
-    if q.dim() != 4 or q.shape[-1] != 64 or q.shape[2] != params.num_heads:
-        raise ValueError("q must be [nlayers][B][H][64]")
-    nl, B = q.shape[:2]
-    _dev(q_pos, "q_pos", torch.int32)
-    _dev(seq_slot0, "seq_slot0", torch.int64)
-    _dev(seq_len, "seq_len", torch.int32)
-    for name, t in (("pi", pi), ("lut_k", lut_k), ("lut_v", lut_v), ("qjl_s", qjl_s)):
-        _dev(t, name, torch.float32)
-    if ebar is not None:
-        _dev(ebar, "ebar", torch.float32)
-    out_dtype = torch.float32 if (params.flags & OUT_FP32 or params.io_dtype == torch.float32) \
-        else torch.float16
-    if out is None:
-        out = torch.empty(q.shape, dtype=out_dtype, device=q.device)
-    _dev(out, "out", out_dtype)
-    need = decode_workspace_bytes(params, B, nl, max_len)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.zeros(need, dtype=torch.uint8, device=q.device)
-    p = params.c()
-    c = cache.c()
-    wsz = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(L.tq_decode_attend(ctypes.byref(p), ctypes.byref(c), _ptr(q), B, layer0, nl, _ptr(q_pos),
-                              _ptr(seq_slot0), _ptr(seq_len), int(max_len), _ptr(pi), _ptr(lut_k),
-                              _ptr(lut_v), _ptr(qjl_s), _ptr(ebar), _ptr(out), _ptr(workspace),
-                              wsz, _stream(q.device)))
+    shape = _decode_checks(params, q, (), q_pos, "q_pos", seq_slot0, seq_len, pi, lut_k, lut_v, qjl_s, ebar)
+    nl, B = shape[0], shape[1]
+    out = _decode_out(params, q, out)
+    p = ctypes.byref(params.c())
+    max_len = int(max_len)
+    workspace, wsz = _decode_workspace(L, p, B, nl, max_len, workspace, q.device)
+    _check(L.tq_decode_attend(p, ctypes.byref(cache.c()), q.data_ptr(), B, layer0, nl, q_pos.data_ptr(),
+                              seq_slot0.data_ptr(), seq_len.data_ptr(), max_len, pi.data_ptr(), lut_k.data_ptr(),
+                              lut_v.data_ptr(), qjl_s.data_ptr(), _ptr(ebar), out.data_ptr(), _ptr(workspace), wsz,
+                              _stream(q.device)))
     return out
 
 
@@ -251,27 +313,13 @@ def decode_attend_noalloc(params: Params, cache: Cache, q, q_pos, seq_slot0, seq
     (see tq_decode_attend_noalloc). ``out`` should be passed where nothing may
     be allocated."""
     L = _load()
-    _dev(q, "q", params.io_dtype)
-    if q.dim() != 4 or q.shape[-1] != 64 or q.shape[2] != params.num_heads:
-        raise ValueError("q must be [nlayers][B][H][64]")
-    nl, B = q.shape[:2]
-    _dev(q_pos, "q_pos", torch.int32)
-    _dev(seq_slot0, "seq_slot0", torch.int64)
-    _dev(seq_len, "seq_len", torch.int32)
-    for name, t in (("pi", pi), ("lut_k", lut_k), ("lut_v", lut_v), ("qjl_s", qjl_s)):
-        _dev(t, name, torch.float32)
-    if ebar is not None:
-        _dev(ebar, "ebar", torch.float32)
-    out_dtype = torch.float32 if (params.flags & OUT_FP32 or params.io_dtype == torch.float32) \
-        else torch.float16
-    if out is None:
-        out = torch.empty(q.shape, dtype=out_dtype, device=q.device)
-    _dev(out, "out", out_dtype)
-    p = params.c()
-    c = cache.c()
-    _check(L.tq_decode_attend_noalloc(ctypes.byref(p), ctypes.byref(c), _ptr(q), B, layer0, nl, _ptr(q_pos),
-                                      _ptr(seq_slot0), _ptr(seq_len), int(max_len), _ptr(pi), _ptr(lut_k),
-                                      _ptr(lut_v), _ptr(qjl_s), _ptr(ebar), _ptr(out), _stream(q.device)))
+    shape = _decode_checks(params, q, (), q_pos, "q_pos", seq_slot0, seq_len, pi, lut_k, lut_v, qjl_s, ebar)
+    nl, B = shape[0], shape[1]
+    out = _decode_out(params, q, out)
+    _check(L.tq_decode_attend_noalloc(ctypes.byref(params.c()), ctypes.byref(cache.c()), q.data_ptr(), B, layer0, nl,
+                                      q_pos.data_ptr(), seq_slot0.data_ptr(), seq_len.data_ptr(), int(max_len),
+                                      pi.data_ptr(), lut_k.data_ptr(), lut_v.data_ptr(), qjl_s.data_ptr(), _ptr(ebar),
+                                      out.data_ptr(), _stream(q.device)))
     return out
 
 
@@ -316,34 +364,15 @@ def decode_step(params: Params, cache: Cache, q, k, v, pos, seq_slot0, seq_len, 
     seq_len holds the tokens cached before the step; the step attends over
     seq_len + 1 of them. Returns out [nlayers][B][H][64]."""
     L = _load()
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        _dev(t, name, params.io_dtype)
-    if q.dim() != 4 or q.shape[-1] != 64 or q.shape[2] != params.num_heads:
-        raise ValueError("q must be [nlayers][B][H][64]")
-    if k.shape != q.shape or v.shape != q.shape:
-        raise ValueError("k and v must have the shape of q")
-    nl, B = q.shape[:2]
-    _dev(pos, "pos", torch.int32)
-    _dev(seq_slot0, "seq_slot0", torch.int64)
-    _dev(seq_len, "seq_len", torch.int32)
-    for name, t in (("pi", pi), ("lut_k", lut_k), ("lut_v", lut_v), ("qjl_s", qjl_s)):
-        _dev(t, name, torch.float32)
-    if ebar is not None:
-        _dev(ebar, "ebar", torch.float32)
-    out_dtype = torch.float32 if (params.flags & OUT_FP32 or params.io_dtype == torch.float32) \
-        else torch.float16
-    if out is None:
-        out = torch.empty(q.shape, dtype=out_dtype, device=q.device)
-    _dev(out, "out", out_dtype)
-    need = decode_workspace_bytes(params, B, nl, max_len)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.zeros(need, dtype=torch.uint8, device=q.device)
-    p = params.c()
-    c = cache.c()
-    wsz = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(L.tq_decode_step(ctypes.byref(p), ctypes.byref(c), _ptr(q), _ptr(k), _ptr(v), B, layer0, nl,
-                            _ptr(pos), _ptr(seq_slot0), _ptr(seq_len), int(max_len), _ptr(pi),
-                            _ptr(lut_k), _ptr(lut_v), _ptr(qjl_s), _ptr(ebar), _ptr(out),
+    shape = _decode_checks(params, q, (k, v), pos, "pos", seq_slot0, seq_len, pi, lut_k, lut_v, qjl_s, ebar)
+    nl, B = shape[0], shape[1]
+    out = _decode_out(params, q, out)
+    p = ctypes.byref(params.c())
+    max_len = int(max_len)
+    workspace, wsz = _decode_workspace(L, p, B, nl, max_len, workspace, q.device)
+    _check(L.tq_decode_step(p, ctypes.byref(cache.c()), q.data_ptr(), k.data_ptr(), v.data_ptr(), B, layer0, nl,
+                            pos.data_ptr(), seq_slot0.data_ptr(), seq_len.data_ptr(), max_len, pi.data_ptr(),
+                            lut_k.data_ptr(), lut_v.data_ptr(), qjl_s.data_ptr(), _ptr(ebar), out.data_ptr(),
                             _ptr(workspace), wsz, _stream(q.device)))
     return out
 
