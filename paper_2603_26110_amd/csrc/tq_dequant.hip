@@ -19,6 +19,8 @@
 // so are the estimates; a thread then writes 16 dimensions of a key row with
 // two 16-byte stores, and the value rows (dimension-major codes) are
 // transposed through LDS before their 16-byte stores.
+#include <algorithm>
+
 #include "tq_device.hpp"
 #include "tq_internal.hpp"
 
@@ -26,15 +28,17 @@ namespace tq {
 
 namespace {
 
-constexpr int kTilesPerBlock = 4;
+constexpr int kMostTiles = 4;       // tiles per block, at most
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 
 }  // namespace
 
 // Block: 4 waves; wave w computes tokens 32 (w & 1) .. +31 (mb) and dimensions
-// 32 (w >> 1) .. +31 (nb) of each tile. Grid: x = ceil(tiles / 4), y = B*H,
-// z = nlayers. Instruction layout (lane l, n = l % 32, h = l / 32): A lane
+// 32 (w >> 1) .. +31 (nb) of each tile. Grid: x = ceil(tiles / block_tiles),
+// y = B*H, z = nlayers. Four waves per SIMD (128 registers) take 63.0 us where
+// three take 66.3 us (660 units x 1024 tokens); with V signs the estimates of
+// both leave three. Instruction layout (lane l, n = l % 32, h = l / 32): A lane
 // values A[n][8h + j], B lane values B[8h + j][n] (j = 0..7), result register
 // r D[8 (r/4) + 4h + r%4][n]. Step q contracts sign index i = 16q + 8h + j,
 // i.e. the sign byte of key word 2q + h of the lane's token.
@@ -60,7 +64,8 @@ __device__ __forceinline__ half8 signs8(uint32_t byte) {
 }
 
 template <bool VQJL>
-__global__ __launch_bounds__(256) void dequant_kernel(DequantArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(VQJL ? 3 : 4)))
+void dequant_kernel(DequantArgs a, int block_tiles) {
   __shared__ __attribute__((aligned(16))) uint4 s_k[128];      // K tile: chunk (c, r) at c*64 + r
   __shared__ __attribute__((aligned(16))) uint4 s_v[128];      // V tile: chunk (c, i) at c*64 + i
   __shared__ __attribute__((aligned(16))) uint2 s_sc[64];      // [n_k | g_k, n_v | g_v] per slot
@@ -82,9 +87,9 @@ __global__ __launch_bounds__(256) void dequant_kernel(DequantArgs a) {
   if (!levels_ascending(load_levels(a.lut_k + lh * 8)) || !levels_ascending(load_levels(a.lut_v + lh * 8)))
     return;
   const int ntiles = (len + 63) >> 6;
-  const int tile_first = blockIdx.x * kTilesPerBlock;
+  const int tile_first = blockIdx.x * block_tiles;
   if (tile_first >= ntiles) return;   // block-uniform, before any barrier
-  const int tile_last = min(ntiles, tile_first + kTilesPerBlock);
+  const int tile_last = min(ntiles, tile_first + block_tiles);
 
   const uint4* kt = reinterpret_cast<const uint4*>(a.k_codes + lh * a.slots * 32);
   const uint4* vt = reinterpret_cast<const uint4*>(a.v_codes + lh * a.slots * 32);
@@ -248,13 +253,19 @@ __global__ __launch_bounds__(256) void dequant_kernel(DequantArgs a) {
   }
 }
 
+// Tiles per block: four where that leaves four blocks for each of the 256
+// compute units (a block's staging of S, 32 loads and splits per thread, then
+// serves four tiles), fewer where it does not: 16 tiles x 20 units take 7.5 us
+// with two and 11.2 us with four tiles per block, 16 x 660 units 72.8 and 63.0 us.
 hipError_t launch_dequantize(const DequantArgs& a, hipStream_t st) {
-  const int ntiles = (a.max_len + 63) / 64;
-  dim3 grid((ntiles + kTilesPerBlock - 1) / kTilesPerBlock, a.B * a.H, a.nlayers);
+  const int ntiles = (int)(((int64_t)a.max_len + 63) / 64);
+  const int64_t tiles = (int64_t)ntiles * a.B * a.H * a.nlayers;
+  const int block_tiles = (int)std::max<int64_t>(1, std::min<int64_t>(kMostTiles, tiles / 1024));
+  dim3 grid((ntiles + block_tiles - 1) / block_tiles, a.B * a.H, a.nlayers);
   if (a.flags & kVQjl)
-    hipLaunchKernelGGL(dequant_kernel<true>, grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL(dequant_kernel<true>, grid, dim3(256), 0, st, a, block_tiles);
   else
-    hipLaunchKernelGGL(dequant_kernel<false>, grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL(dequant_kernel<false>, grid, dim3(256), 0, st, a, block_tiles);
   return hipGetLastError();
 }
 
