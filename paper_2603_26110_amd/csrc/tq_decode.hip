@@ -52,6 +52,8 @@
 //             sign bits.
 // Work items are dealt so that all splits of a unit land on one XCD (blocks
 // go to the 8 XCDs round-robin), where Pi stays in that XCD's L2.
+#include <type_traits>
+
 #include "tq_append.hpp"
 #include "tq_device.hpp"
 #include "tq_internal.hpp"
@@ -135,6 +137,20 @@ __device__ __forceinline__ void store_out(const DecodeArgs& a, int64_t unit, int
     reinterpret_cast<float*>(a.out)[unit * kDim + k] = v;
 }
 
+// A load of cache bytes; STREAM: with the non-temporal hint.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <bool STREAM>
+__device__ __forceinline__ uint4 cache_load16(const uint8_t* p) {
+  if constexpr (!STREAM) return *reinterpret_cast<const uint4*>(p);
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+template <bool STREAM>
+__device__ __forceinline__ uint2 cache_load8(const uint2* p) {
+  if constexpr (!STREAM) return *p;
+  return __builtin_bit_cast(uint2, __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)));
+}
+
 struct TileRegs {
   uint4 k0, k1, v0, v1;
   uint2 sc;
@@ -143,14 +159,15 @@ struct TileRegs {
 // A tile's loads in the order they are used: the key planes, then the scalars
 // (the score needs n_k and g_k), then the value planes, so that the score's
 // wait does not include the value planes.
+template <bool STREAM>
 __device__ __forceinline__ void load_tile(TileRegs& r, const uint8_t* kreg, const uint8_t* vreg,
                                           const uint2* sreg, int64_t gt, int64_t s0, int tt,
                                           int lane) {
-  r.k0 = *reinterpret_cast<const uint4*>(kreg + tile_half_offset(gt, 0, lane));
-  r.k1 = *reinterpret_cast<const uint4*>(kreg + tile_half_offset(gt, 1, lane));
-  r.sc = sreg[s0 + (int64_t)tt * kTile + lane];
-  r.v0 = *reinterpret_cast<const uint4*>(vreg + tile_half_offset(gt, 0, lane));
-  r.v1 = *reinterpret_cast<const uint4*>(vreg + tile_half_offset(gt, 1, lane));
+  r.k0 = cache_load16<STREAM>(kreg + tile_half_offset(gt, 0, lane));
+  r.k1 = cache_load16<STREAM>(kreg + tile_half_offset(gt, 1, lane));
+  r.sc = cache_load8<STREAM>(sreg + s0 + (int64_t)tt * kTile + lane);
+  r.v0 = cache_load16<STREAM>(vreg + tile_half_offset(gt, 0, lane));
+  r.v1 = cache_load16<STREAM>(vreg + tile_half_offset(gt, 1, lane));
 }
 
 
@@ -276,7 +293,7 @@ struct Lut8 {
 };
 
 
-template <int WAVES, bool VQJL>
+template <int WAVES, bool VQJL, bool STREAM>
 __global__ __launch_bounds__(WAVES * 64)
 __attribute__((amdgpu_waves_per_eu((WAVES == 8 && !VQJL) ? 6 : 1)))
 void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
@@ -586,7 +603,7 @@ void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
       const int tq = min(tile_begin + wave + d * WAVES, tile_end_main - 1);   // (a wave without tiles re-reads one)
-      load_tile(buf[d], kreg, vreg, sreg, tile0 + tq, s0, tq, lane);
+      load_tile<STREAM>(buf[d], kreg, vreg, sreg, tile0 + tq, s0, tq, lane);
     }
   }
   // An attend's last token: its key words and scalars (every lane the same
@@ -679,7 +696,7 @@ void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
         value_sign_word<7>(tg, vw[7], sg);
       }
       const int tn = tt + DEPTH * WAVES;
-      if (tn < tile_end_main) load_tile(buf[d], kreg, vreg, sreg, tile0 + tn, s0, tn, lane);
+      if (tn < tile_end_main) load_tile<STREAM>(buf[d], kreg, vreg, sreg, tile0 + tn, s0, tn, lane);
     }
   }
 
@@ -938,28 +955,40 @@ void decode_plan(int units, int max_len, int* waves, int* nsplit, int* split_til
   *nsplit = (ntiles + st - 1) / st;
 }
 
+// From this many token-heads on (300 MB of codes and scalars, by max_len) the
+// tiles are loaded with the non-temporal hint. Up to there a step may find the
+// cache that the step before read in the 256 MB Infinity Cache, and the hint
+// gives that up; beyond, lines pushed out before their next use only cost the
+// fills. 8 waves, 40 heads x 8192 tokens, steps on the same cache, us without /
+// with the hint: 284 MB 53.6 / 55.6, 308 MB 73.3 / 71.3, 379 MB 91.5 / 78.5,
+// 1514 MB 295 / 264; 16 waves, 302 MB 56.7 / 56.0; 4 waves, 480 MB 163 / 158.
+// A step after other kernels filled the Infinity Cache with written data gains
+// more (379 MB 148 / 83), as its reads then push out no dirty lines.
+constexpr int64_t kStreamTokenHeads = 300000000 / 72;
+
 hipError_t launch_decode(const DecodeArgs& a, int waves, hipStream_t st) {
   const int64_t units = (int64_t)a.nlayers * a.B * a.H;
   const int64_t total = units * a.nsplit;
   const int64_t per_xcd = (total + kXcds - 1) / kXcds;
   const int64_t blocks = per_xcd * kXcds;
   const bool vq = (a.flags & kVQjl) != 0;
-  if (waves == 16) {
-    if (vq)
-      hipLaunchKernelGGL((decode_kernel<16, true>), dim3((unsigned)blocks), dim3(1024), 0, st, a, (int)total, (int)per_xcd);
+  const bool stream = units * a.max_len > kStreamTokenHeads;
+  auto launch = [&](auto kernel, int w) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(w * 64), 0, st, a, (int)total, (int)per_xcd);
+  };
+  auto with_waves = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    if (stream)
+      vq ? launch(decode_kernel<W, true, true>, W) : launch(decode_kernel<W, false, true>, W);
     else
-      hipLaunchKernelGGL((decode_kernel<16, false>), dim3((unsigned)blocks), dim3(1024), 0, st, a, (int)total, (int)per_xcd);
-  } else if (waves == 8) {
-    if (vq)
-      hipLaunchKernelGGL((decode_kernel<8, true>), dim3((unsigned)blocks), dim3(512), 0, st, a, (int)total, (int)per_xcd);
-    else
-      hipLaunchKernelGGL((decode_kernel<8, false>), dim3((unsigned)blocks), dim3(512), 0, st, a, (int)total, (int)per_xcd);
-  } else {
-    if (vq)
-      hipLaunchKernelGGL((decode_kernel<4, true>), dim3((unsigned)blocks), dim3(256), 0, st, a, (int)total, (int)per_xcd);
-    else
-      hipLaunchKernelGGL((decode_kernel<4, false>), dim3((unsigned)blocks), dim3(256), 0, st, a, (int)total, (int)per_xcd);
-  }
+      vq ? launch(decode_kernel<W, true, false>, W) : launch(decode_kernel<W, false, false>, W);
+  };
+  if (waves == 16)
+    with_waves(std::integral_constant<int, 16>{});
+  else if (waves == 8)
+    with_waves(std::integral_constant<int, 8>{});
+  else
+    with_waves(std::integral_constant<int, 4>{});
   return hipGetLastError();
 }
 
