@@ -353,9 +353,9 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": traffic_src,
-                     "kernel": ("decode_kernel<8, false> (one launch per tq_decode_attend call)"
+                     "kernel": ("decode_kernel<8, false, false> (one launch per tq_decode_attend call)"
                                 if args.decode_only else
-                                "decode_kernel<8, false> (one launch per tq_decode_step call)"),
+                                "decode_kernel<8, false, false> (one launch per tq_decode_step call)"),
                      "alg_bytes_per_launch": int(alg_bytes)},
         "cpu_baseline": cpu,
         "configs": extra or None,
@@ -593,7 +593,7 @@ def workload_line(torch, tq, synth, name, replays, cpu_seconds, eager=False, cpu
             "roofline": {"bound": "hbm", "achieved": round(alg_bytes / (ms * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                          "unit": "GB/s", "frac": round(alg_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                          "alg_bytes_per_launch": int(alg_bytes),
-                         "kernel": "decode_kernel<8, false> (one launch per tq_decode_step call)"},
+                         "kernel": "decode_kernel<8, false, true> (one launch per tq_decode_step call)"},
             "calibration_s": round(calib_s, 3),
             "prefill_quantize_ms": round(pf_ms, 3),
             "prefill_token_heads": int(tok)}
