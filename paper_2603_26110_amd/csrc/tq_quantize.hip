@@ -770,9 +770,9 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       if (!paper) {
         sb = projected_signs<VQJL>(x, qo.g, s_sh, s_sl, snmax, a.qjl_s, lane);
       } else {
-        uint32_t neg[2] = {0u, 0u};            // (the sign of r: -0 is not below 0)
+        uint32_t neg[2] = {0u, 0u};            // (the sign of r: -0 is not below 0, nor is a NaN of either sign)
 #pragma unroll
-        for (int i = kDim - 1; i >= 0; --i) neg[i >> 5] = push_sign(neg[i >> 5], x[i] + 0.0f);
+        for (int i = kDim - 1; i >= 0; --i) neg[i >> 5] = push_sign(neg[i >> 5], fminf(x[i] + 0.0f, INFINITY));
         sb = ~(((uint64_t)neg[1] << 32) | neg[0]);
       }
 

@@ -151,3 +151,22 @@ def test_short_sequences_in_a_batch_equal_each_alone(T, lens, flags, io):
                          seq_tokens=None if lens is None else tokens[b:b + 1].clone())
     for x, y in zip(_planes(batch), _planes(each)):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("flags", [tq.QJL_PAPER, tq.QJL_PAPER | tq.V_QJL])
+def test_element_signs_of_vectors_with_nan(flags):
+    # sign_i = !(r_i < 0): a NaN residual, of either sign bit, has sign 1. Against
+    # calls of 16 tokens, which another kernel takes.
+    T, H = 96, 2
+    flags |= tq.INPUT_ROTATED
+    case = Case(84, 1, H, 1, T, io="f32", flags=flags, slots=128)
+    for x in (case.k, case.v):
+        x[0, 0, 3::16, :, 5] = np.inf                        # u = inf * 0 there
+        x[0, 0, 5::16, :, 7] = np.nan
+        x.view(np.uint32)[0, 0, 7::16, :, 9] = 0xFFC00000     # NaN with the sign bit set
+    whole, parts = tq.Cache(1, H, 128), tq.Cache(1, H, 128)
+    case.gpu_quantize(whole)
+    for j in range(0, T, 16):
+        case.gpu_quantize(parts, k=case.t("k")[:, :, j:j + 16].contiguous(), v=case.t("v")[:, :, j:j + 16].contiguous(),
+                          pos0=[j], slot0=[j])
+    assert all(torch.equal(x, y) for x, y in zip(_planes(whole), _planes(parts)))
