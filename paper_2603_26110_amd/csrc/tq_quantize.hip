@@ -113,8 +113,11 @@ __device__ __forceinline__ void split8(const float* v, float sc, half8& hi, half
 }
 
 // 2^(1 - e) for m = f 2^e, f in [0.5, 1): m times it lies in [1, 2); 1 for m = 0.
+// At most 2^126, so that it and its reciprocal are normal numbers: a subnormal
+// m then lands below 1, in multiples of 2^-23, which two fp16 parts hold
+// exactly.
 __device__ __forceinline__ float unit_scale(float m) {
-  const float s = ldexpf(1.0f, 1 - __builtin_amdgcn_frexp_expf(m));
+  const float s = ldexpf(1.0f, min(1 - __builtin_amdgcn_frexp_expf(m), 126));
   return m > 0.0f ? s : 1.0f;
 }
 

@@ -170,3 +170,23 @@ def test_element_signs_of_vectors_with_nan(flags):
         case.gpu_quantize(parts, k=case.t("k")[:, :, j:j + 16].contiguous(), v=case.t("v")[:, :, j:j + 16].contiguous(),
                           pos0=[j], slot0=[j])
     assert all(torch.equal(x, y) for x, y in zip(_planes(whole), _planes(parts)))
+
+
+@pytest.mark.parametrize("flags", [tq.V_ROTATE, tq.V_ROTATE | tq.V_QJL])
+def test_subnormal_fp32_vectors(flags):
+    # largest entries of 2^-121 to 2^-149 and exact zeros: every square underflows,
+    # so n = 0 and the codes are those of a zero vector, as in calls of 16 tokens
+    T, H = 96, 2
+    case = Case(85, 1, H, 1, T, io="f32", flags=flags, slots=128)
+    g = synth.rng(86)
+    for x in (case.k, case.v):
+        e = -121.0 - (np.arange(T) % 29)
+        x[:] = (g.uniform(-1, 1, x.shape) * 2.0 ** e[:, None, None]).astype(np.float32)
+        x[..., ::3] = 0.0
+    whole, parts = tq.Cache(1, H, 128), tq.Cache(1, H, 128)
+    case.gpu_quantize(whole)
+    for j in range(0, T, 16):
+        case.gpu_quantize(parts, k=case.t("k")[:, :, j:j + 16].contiguous(), v=case.t("v")[:, :, j:j + 16].contiguous(),
+                          pos0=[j], slot0=[j])
+    assert not whole.scalars.view(-1, 4)[:T, [0, 2]].any()
+    assert all(torch.equal(x, y) for x, y in zip(_planes(whole), _planes(parts)))
