@@ -74,6 +74,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
 constexpr int kGroup = 32;                   // tokens per wave
+constexpr float kSignBand = 0x1p-15f;        // projected_signs' guard band
 
 // 16-byte chunk c (columns 8c .. 8c + 7) of row r of a staged 64 x 64 matrix
 // of fp16 lies at chunk position c ^ (r / 2 % 8) of its row: the 16 rows read
@@ -395,12 +396,17 @@ __device__ __forceinline__ uint32_t nibbles_to_bytes(uint32_t x) {
 // with BOTH its key or value): bit i = !(p_i < 0) for p_i the binary32 fma
 // chain over k ascending of S[i][k] r_k (the exact quantizer step).
 // p~ = (sigma_i S_i) . (s r) comes from the matrix cores (sigma_i, s: the
-// row's and the vector's power-of-two scales; s brings ||r|| = g into [1, 2)).
-// Any evaluation of it there is within 2^-17.3 ||sigma_i S_i|| ||s r|| of its
-// exact value (2^-20.4 for the split products, 2^-21 for the fp16 spacing
-// below 2^-14, 2^-18.2 for 28 fp32 additions per sum, truncated at worst) and
-// the chain within 2^-18 of that, 2^-16.6 in all, so where
-// |p~_i| > 2^-16 max_i ||sigma_i S_i|| ||s r|| the signs agree. The smallest
+// row's and the vector's power-of-two scales; s brings ||r|| = g into [1, 2)),
+// and its sign is taken where |p~_i| > kSignBand max_i ||sigma_i S_i|| ||s r||.
+// There it is the chain's, whatever order and rounding the matrix cores sum a
+// row's 192 products in. In units of ||sigma_i S_i|| ||s r||: where the signs
+// differ the exact sum is next to 0, so its partial sums are at most 1/2
+// (Cauchy-Schwarz on the two parts); one addition per product, truncated to
+// fp32, then errs by up to 192 x 2^-24 = 2^-16.4, the split products by
+// 2^-20.4, the fp16 spacing below 2^-14 by 2^-21 and the chain by 2^-19:
+// 2^-16.1 in all, and kSignBand is twice that. (2^-16 would save 0.7 us of
+// 13.1 for 1024 tokens of 20 heads, with no room; 2^-14 cost 1.6 us more.)
+// The smallest
 // |p~_i| tells whether any coordinate lies inside that band (snmax: the
 // largest row norm, infinite if a row is not finite); only then are the rows
 // found, and recomputed with the chain from S in memory for all the wave's
@@ -439,7 +445,7 @@ __device__ __forceinline__ uint64_t projected_signs(float (&x)[kDim], float g, c
   if constexpr (BOTH) {
     float p[kDim];
     to_lane_per_vector(acc, p);
-    const float band = snmax * (g * sc) * 0x1p-16f;
+    const float band = snmax * (g * sc) * kSignBand;
     float least[4];                            // of dimensions 16 e .. 16 e + 15
     uint32_t neg[2];
 #pragma unroll
@@ -464,7 +470,7 @@ __device__ __forceinline__ uint64_t projected_signs(float (&x)[kDim], float g, c
       }
     }
   } else {
-    const float band = snmax * ((lane < 32 ? g : g_other) * sk) * 0x1p-16f;
+    const float band = snmax * ((lane < 32 ? g : g_other) * sk) * kSignBand;
     float least[4];                            // of registers 8 e .. 8 e + 7
     uint32_t neg = 0;                          // nibble w: dimensions 8 w + 4 h + j
 #pragma unroll

@@ -132,7 +132,7 @@ def test_quantize_bit_exact_at_thresholds(T, flags):
 @pytest.mark.parametrize("flags", [tq.V_ROTATE, tq.V_ROTATE | tq.V_QJL])
 def test_projected_signs_inside_the_guard_band_are_exact(flags):
     # The tile kernel takes a projected sign from its matrix-core product only
-    # where |p_i| > 2^-14 ||S_i|| ||r|| and runs the fixed-order chain
+    # where |p_i| > 2^-15 max ||S_i|| ||r|| and runs the fixed-order chain
     # elsewhere. Rows of S built to land in that band: a zero row (p = 0,
     # sign +1), a row of tiny entries, rows with one nonzero entry (exact
     # products), and a row that cancels to a few ulps for most residuals.

@@ -190,3 +190,46 @@ def test_subnormal_fp32_vectors(flags):
                           pos0=[j], slot0=[j])
     assert not whole.scalars.view(-1, 4)[:T, [0, 2]].any()
     assert all(torch.equal(x, y) for x, y in zip(_planes(whole), _planes(parts)))
+
+
+@pytest.mark.parametrize("flags", [0, tq.V_QJL])
+def test_projected_signs_around_the_guard_band(flags):
+    # Rows of S with S_i . r / (||S_i|| ||r||) spread over 2^-20 .. 2^-12, of both
+    # signs, for the one residual direction that all tokens of a call share (a
+    # vector times powers of two), half of them with partial sums that grow to
+    # half of ||S_i|| ||r|| before they cancel: every sign is the chain's.
+    g = synth.rng(87)
+    T = 64
+    for turn in range(12):
+        case = Case(88, 1, 1, 1, T, io="f32", flags=flags | tq.INPUT_ROTATED, slots=64)
+        x = g.standard_normal(64).astype(np.float32)
+        idx, r = _residual(x, case.lut_k[0, 0])
+        rd = r.astype(np.float64)
+        unit = rd / np.linalg.norm(rd)
+        S = g.standard_normal((64, 64))
+        S[32:] = np.abs(S[32:]) * np.sign(rd) * np.where(np.arange(64) < 32, 1.0, -1.0)
+        S[32:, 32:] *= (S[32:, :32] @ rd[:32] / -(S[32:, 32:] @ rd[32:]))[:, None]
+        S -= (S @ unit)[:, None] * unit
+        share = 2.0 ** np.linspace(-20, -12, 32) * np.where(np.arange(32) % 2 == turn % 2, 1.0, -1.0)
+        S += np.concatenate([share, share])[:, None] * np.linalg.norm(S, axis=1)[:, None] * unit
+        case.S = S.astype(np.float32)
+        case.k[0, 0, :, 0] = x * 2.0 ** (np.arange(T) % 9 - 4)[:, None]
+        case.v = case.k.copy()
+        case.lut_v = case.lut_k.copy()
+        cache = tq.Cache(1, 1, 64)
+        case.gpu_quantize(cache)
+        oc = oracle.Cache(1, 1, 64)
+        case.oracle_quantize(oc)
+        got = device_bytes(cache)
+        np.testing.assert_array_equal(got.k, oc.k)
+        np.testing.assert_array_equal(got.v, oc.v)
+
+
+def _residual(x, lut):
+    """Levels and binary32 residual of a vector, by the quantizer's steps."""
+    s = np.float32(0)
+    for v in x:
+        s = np.float32(np.float64(v) * np.float64(v) + np.float64(s))
+    u = x * np.float32(np.float32(8) / np.sqrt(s))
+    idx = (u[:, None] > np.float32(0.5) * (lut[1:] + lut[:-1])).sum(1)
+    return idx, u - lut[idx]
