@@ -129,40 +129,63 @@ __device__ __forceinline__ float nearest_level(float u, const Levels& L, float c
   return lv;
 }
 
-// The index alone, #{m : u > t_m} (the same count as nearest_level's), for a
-// caller that reads the level itself from a table in LDS. The comparisons
-// write VCC only and each is used at once, so no lane mask stays live across
-// the elements of a vector (64 unrolled select chains keep so many masks
-// live that they spill).
+// The index alone, #{m : u > t_m} (the same count as nearest_level's), of four
+// values at a time, for a caller that reads the level itself from a table in
+// LDS. The comparisons write three scalar register pairs and VCC, and each is
+// used at once, so no lane mask stays live across the elements of a vector (64
+// unrolled select chains keep so many masks live that they spill).
 // The count is the length of the prefix of thresholds below u (they are
 // non-decreasing), found in three steps: b2 = [t3 < u], b1 =
 // [t(b2 ? 5 : 1) < u] and b0 = [t(4 b2 + 2 b1) < u], each bit added into
 // the count by a carry (a NaN u compares false throughout, like the
 // count). The second threshold is selected in registers (t1 and t5 as
-// vector operands: a select that reads VCC cannot also read a scalar);
+// vector operands: a select that reads a mask cannot also read a scalar);
 // the third, t(2 i) for i = 2 b2 + b1, is read from {t0, t2, t4, t6} in LDS.
-// level_half gives i, level_full the count from i and that threshold.
-__device__ __forceinline__ uint32_t level_half(float u, float t1, float t3, float t5) {
-  uint32_t i;
-  float ta;
-  asm("v_cmp_lt_f32 vcc, %2, %5\n\t"
-      "v_cndmask_b32_e64 %0, 0, 1, vcc\n\t"
-      "v_cndmask_b32 %1, %3, %4, vcc\n\t"
-      "v_cmp_lt_f32 vcc, %1, %5\n\t"
-      "v_addc_co_u32 %0, vcc, %0, %0, vcc"
-      : "=&v"(i), "=&v"(ta)
-      : "v"(t3), "v"(t1), "v"(t5), "v"(u)
+// levels_half gives i, levels_full the counts from i and those thresholds.
+// (A vector instruction may read a mask that another wrote only after two wait
+// states, which the compiler does not see here: the four values take turns.)
+__device__ __forceinline__ void levels_half(uint32_t* i, const float* u, float t1, float t3, float t5) {
+  float a0, a1, a2, a3;
+  uint64_t m0, m1, m2;
+  asm("v_cmp_lt_f32_e64 %8, %12, %14\n\t"
+      "v_cmp_lt_f32_e64 %9, %12, %15\n\t"
+      "v_cmp_lt_f32_e64 %10, %12, %16\n\t"
+      "v_cmp_lt_f32 vcc, %12, %17\n\t"
+      "v_cndmask_b32_e64 %0, 0, 1, %8\n\t"
+      "v_cndmask_b32_e64 %4, %11, %13, %8\n\t"
+      "v_cndmask_b32_e64 %1, 0, 1, %9\n\t"
+      "v_cndmask_b32_e64 %5, %11, %13, %9\n\t"
+      "v_cndmask_b32_e64 %2, 0, 1, %10\n\t"
+      "v_cndmask_b32_e64 %6, %11, %13, %10\n\t"
+      "v_cndmask_b32_e64 %3, 0, 1, vcc\n\t"
+      "v_cndmask_b32 %7, %11, %13, vcc\n\t"
+      "v_cmp_lt_f32_e64 %8, %4, %14\n\t"
+      "v_cmp_lt_f32_e64 %9, %5, %15\n\t"
+      "v_cmp_lt_f32_e64 %10, %6, %16\n\t"
+      "v_cmp_lt_f32 vcc, %7, %17\n\t"
+      "v_addc_co_u32_e64 %0, %8, %0, %0, %8\n\t"
+      "v_addc_co_u32_e64 %1, %9, %1, %1, %9\n\t"
+      "v_addc_co_u32_e64 %2, %10, %2, %2, %10\n\t"
+      "v_addc_co_u32 %3, vcc, %3, %3, vcc"
+      : "=&v"(i[0]), "=&v"(i[1]), "=&v"(i[2]), "=&v"(i[3]), "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3), "=&s"(m0),
+        "=&s"(m1), "=&s"(m2)
+      : "v"(t1), "v"(t3), "v"(t5), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3])
       : "vcc");
-  return i;
 }
 
-__device__ __forceinline__ uint32_t level_full(float u, uint32_t i, float tb) {
-  asm("v_cmp_lt_f32 vcc, %1, %2\n\t"
-      "v_addc_co_u32 %0, vcc, %0, %0, vcc"
-      : "+v"(i)
-      : "v"(tb), "v"(u)
+__device__ __forceinline__ void levels_full(uint32_t* i, const float* u, const float* tb) {
+  uint64_t m0, m1, m2;
+  asm("v_cmp_lt_f32_e64 %4, %7, %11\n\t"
+      "v_cmp_lt_f32_e64 %5, %8, %12\n\t"
+      "v_cmp_lt_f32_e64 %6, %9, %13\n\t"
+      "v_cmp_lt_f32 vcc, %10, %14\n\t"
+      "v_addc_co_u32_e64 %0, %4, %0, %0, %4\n\t"
+      "v_addc_co_u32_e64 %1, %5, %1, %1, %5\n\t"
+      "v_addc_co_u32_e64 %2, %6, %2, %2, %6\n\t"
+      "v_addc_co_u32 %3, vcc, %3, %3, vcc"
+      : "+v"(i[0]), "+v"(i[1]), "+v"(i[2]), "+v"(i[3]), "=&s"(m0), "=&s"(m1), "=&s"(m2)
+      : "v"(tb[0]), "v"(tb[1]), "v"(tb[2]), "v"(tb[3]), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3])
       : "vcc");
-  return i;
 }
 
 // Sixteen values loaded before any of them is used: the wave waits for its
@@ -190,16 +213,19 @@ __device__ __forceinline__ QuantOut quantize_lane(float (&xh)[kDim], float scale
     uint32_t idx[16];
     float rd[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      xh[i0 + j] *= inv;               // u_i
-      idx[j] = level_half(xh[i0 + j], t1, t3, t5);
-      rd[j] = thr[idx[j]];
+    for (int j = 0; j < 16; j += 4) {
+#pragma unroll
+      for (int e = j; e < j + 4; ++e) xh[i0 + e] *= inv;   // u_i
+      levels_half(&idx[j], &xh[i0 + j], t1, t3, t5);
+#pragma unroll
+      for (int e = j; e < j + 4; ++e) rd[e] = thr[idx[e]];
     }
     arrive16(rd);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      idx[j] = level_full(xh[i0 + j], idx[j], rd[j]);
-      rd[j] = lev[idx[j]];             // the level c[idx]
+    for (int j = 0; j < 16; j += 4) {
+      levels_full(&idx[j], &xh[i0 + j], &rd[j]);
+#pragma unroll
+      for (int e = j; e < j + 4; ++e) rd[e] = lev[idx[e]];   // the level c[idx]
     }
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
