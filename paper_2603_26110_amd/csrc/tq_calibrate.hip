@@ -355,7 +355,6 @@ struct LutSmem {
   Mass below[kBins + 1];                 // mass of the bins below b
   union {
     double list[7][kWindow];             // the windows' coordinates
-    uint32_t count[kBins];               // the histogram's counts (its sums are in below[b].sum)
     uint32_t coarse[kCoarse];            // the sample's counts
   };
   uint8_t owner[kBins];                  // the window that holds a bin, 0xFF: none
@@ -453,7 +452,7 @@ void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit ini
     }
   }
   __syncthreads();
-  for (int b = t; b < kBins; b += kCalThreads) { sm.count[b] = 0u; sm.below[b].sum = 0; }
+  for (int b = t; b < kBins; b += kCalThreads) sm.below[b] = Mass{0, 0};
   __syncthreads();
 
   // ---- histogram. A NaN coordinate (infinite inputs) belongs to cell 0, as
@@ -466,7 +465,7 @@ void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit ini
         sm.nan = 1;
       } else {
         const int b = bin_of(sm, u[k]);
-        atomicAdd(&sm.count[b], 1u);
+        add_i64(sm.below[b].n, 1);
         add_i64(sm.below[b].sum, fixed_of(u[k], unit));
       }
     }
@@ -479,7 +478,7 @@ void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit ini
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       own[j] = all;
-      all.n += sm.count[t * kPer + j];
+      all.n += sm.below[t * kPer + j].n;
       all.sum += sm.below[t * kPer + j].sum;
     }
     const Mass scan{wave_scan_i64(all.n, lane), wave_scan_i64(all.sum, lane)};

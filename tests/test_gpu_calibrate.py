@@ -98,3 +98,11 @@ def test_rotation_at_every_remainder_and_rank(n):
         gram = y.T @ y
         assert np.max(np.abs(gram - np.diag(np.diag(gram)))) <= 1e-6 * ref[0] ** 2
         assert np.all(np.take_along_axis(pi[h], np.abs(pi[h]).argmax(1)[:, None], 1) > 0)
+
+
+def test_tables_of_more_equal_coordinates_than_32_bits_count():
+    # 2^26 vectors of ones: all 2^32 coordinates are 1, in one bin
+    x = torch.ones((1, 1 << 26, 64), device="cuda")
+    init = np.array([-3, -2, -1, -0.5, 0.5, 1.25, 2, 3], np.float32)
+    got = tq.calibrate_lut(x, None, init, max_iter=1).cpu().numpy()[0]
+    np.testing.assert_array_equal(got, [-3, -2, -1, -0.5, 0.5, 1, 2, 3])
