@@ -332,8 +332,12 @@ __device__ __forceinline__ void each_coordinate(const float* X, int ncal, bool r
 // Sums are kept as integers in units of 2^-sum_bits, so they do not depend on
 // the order in which the lanes arrive. A vector's coordinates have mean square
 // 1, so n of them sum to at most n in magnitude, and sum_bits = 62 - log2 n
-// (44 at 4096 vectors) cannot overflow; a cell's mean is then closer than
-// fp64 sums of its coordinates in sequence.
+// (44 at 4096 vectors, 36 at 2^20) cannot overflow. A coordinate is rounded by
+// up to 2^-(sum_bits + 1), at most fp32's rounding of a level of at least
+// 2^(24 - sum_bits). Where a level ends below that and coordinates below it
+// exist, the table is made again by plain iterations with fp64 sums
+// (plain_lloyd), so that levels far below the others keep their precision and
+// stay apart.
 //
 // What bounds it: the walks, on the one compute unit that a head gets. 20
 // heads x 4096 keys and random rotations take 1.73 ms (144 ms with a walk per
@@ -364,7 +368,9 @@ struct LutSmem {
   Mass above[2][7];
   Mass part[kCalWaves][8];               // a direct walk: each wave's cells
   Mass carry[kCalWaves];
-  int over, nan;
+  double plain[kCalWaves][8];            // plain iterations: each wave's cells
+  int64_t plain_n[kCalWaves][8];
+  int over, nan, tiny;
 };
 
 // Position of u on a grid of kCoarse << kCoarseBits steps over [-8, 8] (0 for NaN).
@@ -405,6 +411,79 @@ __device__ __forceinline__ int64_t wave_scan_i64(int64_t v, int lane) {
   return v;
 }
 
+// Levels in lanes k, k + 8, .. in ascending order (a NaN level, only ever the
+// first, stays first).
+__device__ __forceinline__ double ascending(double fresh, int k) {
+  int rank = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const double lj = __shfl(fresh, j, 64);
+    rank += (lj < fresh || ((lj == fresh || lj != lj) && j < k)) ? 1 : 0;
+  }
+  double lev = fresh;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const double lj = __shfl(fresh, j, 64);
+    lev = __shfl(rank, j, 64) == k ? lj : lev;
+  }
+  return lev;
+}
+
+// The iteration as it is defined: a walk each, every lane summing its
+// coordinates' cells in fp64 in a fixed order. (Not inlined: its registers
+// would be spilled from calibrate_lut_kernel's loops.)
+__device__ __attribute__((noinline)) double plain_lloyd(LutSmem& sm, const float* X, int ncal, const float* pi,
+                                                        LutInit init, int max_iter, double tol) {
+  const int lane = threadIdx.x & 63, k = lane & 7;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  HeadRotation R;
+  if (pi) load_rotation(R, pi, lane);
+  double lev = 0.0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) lev = k == j ? (double)init.c[j] : lev;
+  for (int it = 0; it < max_iter; ++it) {
+    double tm[7], sum[8];
+    int n[8];
+#pragma unroll
+    for (int m = 0; m < 7; ++m) tm[m] = 0.5 * (__shfl(lev, m, 64) + __shfl(lev, m + 1, 64));
+#pragma unroll
+    for (int c = 0; c < 8; ++c) { sum[c] = 0.0; n[c] = 0; }
+    each_coordinate(X, ncal, pi != nullptr, R, wave, lane, 1, [&](const double (&u)[16], bool live) {
+      if (!live) return;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        int at = 0;
+#pragma unroll
+        for (int m = 0; m < 7; ++m) at += (u[j] > tm[m]) ? 1 : 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          sum[c] += at == c ? u[j] : 0.0;
+          n[c] += at == c ? 1 : 0;
+        }
+      }
+    });
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const double s = wave_sum_f64(sum[c]);
+      const int64_t cnt = wave_sum_i64(n[c]);
+      if (lane == 0) { sm.plain[wave][c] = s; sm.plain_n[wave][c] = cnt; }
+    }
+    __syncthreads();
+    double s = 0.0;
+    int64_t cnt = 0;
+    for (int w = 0; w < kCalWaves; ++w) { s += sm.plain[w][k]; cnt += sm.plain_n[w][k]; }
+    __syncthreads();
+    const double fresh = cnt > 0 ? s / (double)cnt : lev;
+    double delta = fabs(fresh - lev);
+    delta = (delta == delta) ? delta : 0.0;
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) delta = fmax(delta, __shfl_xor(delta, o, 64));
+    lev = ascending(fresh, k);
+    if (delta < tol) break;                // (the same in every wave)
+  }
+  return lev;
+}
+
 __global__ __launch_bounds__(kCalThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit init, int max_iter, double tol,
                           int sum_bits, float* lut_out) {
@@ -414,11 +493,11 @@ void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit ini
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const float* X = x + (int64_t)head * ncal * kDim;
   const bool rot = pi != nullptr;
-  const double unit = ldexp(1.0, sum_bits);
+  const double unit = ldexp(1.0, sum_bits), least = ldexp(1.0, 24 - sum_bits);
   HeadRotation R;
   if (rot) load_rotation(R, pi + (int64_t)head * kDim * kDim, lane);
   if (t < 7) { sm.wa[t] = 0; sm.wb[t] = 0; }
-  if (t == 0) { sm.over = 0; sm.nan = 0; }
+  if (t == 0) { sm.over = 0; sm.nan = 0; sm.tiny = 0; }
   for (int c = t; c < kCoarse; c += kCalThreads) sm.coarse[c] = 0u;
   __syncthreads();
 
@@ -467,6 +546,7 @@ void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit ini
         const int b = bin_of(sm, u[k]);
         add_i64(sm.below[b].n, 1);
         add_i64(sm.below[b].sum, fixed_of(u[k], unit));
+        if (fabs(u[k]) < least && u[k] != 0.0) sm.tiny = 1;
       }
     }
   });
@@ -650,20 +730,11 @@ void calibrate_lut_kernel(const float* x, int ncal, const float* pi, LutInit ini
     delta = (delta == delta) ? delta : 0.0;
 #pragma unroll
     for (int o = 1; o < 8; o <<= 1) delta = fmax(delta, __shfl_xor(delta, o, 64));
-    // ascending order (a NaN level, only ever the first, stays first)
-    int rank = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const double lj = __shfl(fresh, j, 64);
-      rank += (lj < fresh || ((lj == fresh || lj != lj) && j < k)) ? 1 : 0;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const double lj = __shfl(fresh, j, 64);
-      lev = __shfl(rank, j, 64) == k ? lj : lev;
-    }
+    lev = ascending(fresh, k);
     if (delta < tol) break;                // (the same in every wave)
   }
+  if (sm.tiny != 0 && __builtin_amdgcn_ballot_w64(fabs(lev) < ldexp(1.0, 24 - sum_bits)) != 0)
+    lev = plain_lloyd(sm, X, ncal, pi ? pi + (int64_t)head * kDim * kDim : nullptr, init, max_iter, tol);
   if (t < 8) lut_out[(int64_t)head * 8 + t] = (float)lev;
 }
 

@@ -106,3 +106,21 @@ def test_tables_of_more_equal_coordinates_than_32_bits_count():
     init = np.array([-3, -2, -1, -0.5, 0.5, 1.25, 2, 3], np.float32)
     got = tq.calibrate_lut(x, None, init, max_iter=1).cpu().numpy()[0]
     np.testing.assert_array_equal(got, [-3, -2, -1, -0.5, 0.5, 1, 2, 3])
+
+
+@pytest.mark.parametrize("n,rotate", [(600, False), (129, True), (5000, True)])
+def test_tables_of_coordinates_far_below_the_largest(n, rotate):
+    # one channel 1e15 times the others: levels of 1e-14 come from sums of such
+    # coordinates, beside levels of 8 (two heads, the second without such)
+    g = synth.rng(33)
+    x = g.standard_normal((2, n, 64))
+    x[0, :, 1:] *= 1e-15
+    x = x.astype(np.float32)
+    pi = np.zeros((2, 64, 64), np.float32)
+    pi[:, 0, 0] = 1.0                                      # (the other channels among themselves)
+    pi[:, 1:, 1:] = np.linalg.qr(g.standard_normal((63, 63)))[0]
+    got = tq.calibrate_lut(_d(x), _d(pi) if rotate else None, INIT).cpu().numpy()
+    for h in range(2):
+        ref = oracle.calibrate_lut(x[h], pi[h] if rotate else None, INIT)
+        np.testing.assert_allclose(got[h], ref, rtol=2.0 ** -22, atol=0)
+        assert np.all(np.diff(got[h]) > 0)
