@@ -52,6 +52,7 @@
 //             sign bits.
 // Work items are dealt so that all splits of a unit land on one XCD (blocks
 // go to the 8 XCDs round-robin), where Pi stays in that XCD's L2.
+#include <algorithm>
 #include <type_traits>
 
 #include "tq_append.hpp"
@@ -137,17 +138,17 @@ __device__ __forceinline__ void store_out(const DecodeArgs& a, int64_t unit, int
     reinterpret_cast<float*>(a.out)[unit * kDim + k] = v;
 }
 
-// A load of cache bytes; STREAM: with the non-temporal hint.
+// A load of cache bytes; HINT: with the non-temporal hint.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-template <bool STREAM>
+template <bool HINT>
 __device__ __forceinline__ uint4 cache_load16(const uint8_t* p) {
-  if constexpr (!STREAM) return *reinterpret_cast<const uint4*>(p);
+  if constexpr (!HINT) return *reinterpret_cast<const uint4*>(p);
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
-template <bool STREAM>
+template <bool HINT>
 __device__ __forceinline__ uint2 cache_load8(const uint2* p) {
-  if constexpr (!STREAM) return *p;
+  if constexpr (!HINT) return *p;
   return __builtin_bit_cast(uint2, __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)));
 }
 
@@ -159,16 +160,27 @@ struct TileRegs {
 // A tile's loads in the order they are used: the key planes, then the scalars
 // (the score needs n_k and g_k), then the value planes, so that the score's
 // wait does not include the value planes.
-template <bool STREAM>
+template <bool HINT>
 __device__ __forceinline__ void load_tile(TileRegs& r, const uint8_t* kreg, const uint8_t* vreg,
                                           const uint2* sreg, int64_t gt, int64_t s0, int tt,
                                           int lane) {
-  r.k0 = cache_load16<STREAM>(kreg + tile_half_offset(gt, 0, lane));
-  r.k1 = cache_load16<STREAM>(kreg + tile_half_offset(gt, 1, lane));
-  r.sc = cache_load8<STREAM>(sreg + s0 + (int64_t)tt * kTile + lane);
-  r.v0 = cache_load16<STREAM>(vreg + tile_half_offset(gt, 0, lane));
-  r.v1 = cache_load16<STREAM>(vreg + tile_half_offset(gt, 1, lane));
+  r.k0 = cache_load16<HINT>(kreg + tile_half_offset(gt, 0, lane));
+  r.k1 = cache_load16<HINT>(kreg + tile_half_offset(gt, 1, lane));
+  r.sc = cache_load8<HINT>(sreg + s0 + (int64_t)tt * kTile + lane);
+  r.v0 = cache_load16<HINT>(vreg + tile_half_offset(gt, 0, lane));
+  r.v1 = cache_load16<HINT>(vreg + tile_half_offset(gt, 1, lane));
 }
+
+// From this many token-heads on (300 MB of codes and scalars) the tiles are
+// loaded with the non-temporal hint. Up to there a step may find the cache that
+// the step before read in the 256 MB Infinity Cache, and the hint gives that
+// up; beyond, lines pushed out before their next use only cost the fills. 8
+// waves, 40 heads x 8192 tokens, steps on the same cache, us without / with the
+// hint: 284 MB 53.6 / 55.6, 308 MB 73.3 / 71.3, 379 MB 91.5 / 78.5, 1514 MB 295
+// / 264; 16 waves, 302 MB 56.7 / 56.0; 4 waves, 480 MB 163 / 158. A step after
+// other kernels filled the Infinity Cache with written data gains more (379 MB
+// 148 / 83), as its reads then push out no dirty lines.
+constexpr int64_t kStreamTokenHeads = 300000000 / 72;
 
 
 // (byte 3 of x) << 2, one VALU op (sub-dword operand select).
@@ -433,6 +445,14 @@ void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
   const Lut8 ck = Lut8::of(kw), cvl = Lut8::of(vw);
   const float ebar_k = paper ? ebar_raw : 0.0f;
   const int n = len + len_add;             // tokens attended (the step's new one included)
+  // STREAM: the call may read more than the Infinity Cache keeps, by max_len;
+  // whether it does, by its lengths, which only the device knows: lane i takes
+  // that of sequence i, or of 64 sequences in eight runs over the batch.
+  int len_i = 0;
+  if (STREAM) {
+    const int bi = B <= 64 ? lane : (((lane >> 3) * B) >> 3) + (lane & 7);
+    if (bi < B) len_i = seq_len[bi];
+  }
   // a unit whose sequence range or query position is out of bounds, or
   // whose K or V table is not strictly ascending, is not appended to and
   // gets NaN output. Lanes 0..6 compare their level with the next one (a
@@ -598,13 +618,21 @@ void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
   }
   // Tiles are requested only now (the appending waves' registers hold no
   // tiles through the append).
+  bool hint = false;
+  if (STREAM) {
+    hint = wave_sum_uniform((float)min(max(len_i, 0), a.max_len)) > a.stream_lengths;
+  }
   TileRegs buf[DEPTH];
+  auto load = [&](TileRegs& r, int tt) {
+    if (STREAM && hint)
+      load_tile<true>(r, kreg, vreg, sreg, tile0 + tt, s0, tt, lane);
+    else
+      load_tile<false>(r, kreg, vreg, sreg, tile0 + tt, s0, tt, lane);
+  };
   if (tile_end_main > tile_begin) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int tq = min(tile_begin + wave + d * WAVES, tile_end_main - 1);   // (a wave without tiles re-reads one)
-      load_tile<STREAM>(buf[d], kreg, vreg, sreg, tile0 + tq, s0, tq, lane);
-    }
+    for (int d = 0; d < DEPTH; ++d)
+      load(buf[d], min(tile_begin + wave + d * WAVES, tile_end_main - 1));   // (a wave without tiles re-reads one)
   }
   // An attend's last token: its key words and scalars (every lane the same
   // address) and, per lane, the value word of its dimension that holds the
@@ -696,7 +724,7 @@ void decode_kernel(DecodeArgs a, int total_work, int per_xcd) {
         value_sign_word<7>(tg, vw[7], sg);
       }
       const int tn = tt + DEPTH * WAVES;
-      if (tn < tile_end_main) load_tile<STREAM>(buf[d], kreg, vreg, sreg, tile0 + tn, s0, tn, lane);
+      if (tn < tile_end_main) load(buf[d], tn);
     }
   }
 
@@ -955,24 +983,14 @@ void decode_plan(int units, int max_len, int* waves, int* nsplit, int* split_til
   *nsplit = (ntiles + st - 1) / st;
 }
 
-// From this many token-heads on (300 MB of codes and scalars, by max_len) the
-// tiles are loaded with the non-temporal hint. Up to there a step may find the
-// cache that the step before read in the 256 MB Infinity Cache, and the hint
-// gives that up; beyond, lines pushed out before their next use only cost the
-// fills. 8 waves, 40 heads x 8192 tokens, steps on the same cache, us without /
-// with the hint: 284 MB 53.6 / 55.6, 308 MB 73.3 / 71.3, 379 MB 91.5 / 78.5,
-// 1514 MB 295 / 264; 16 waves, 302 MB 56.7 / 56.0; 4 waves, 480 MB 163 / 158.
-// A step after other kernels filled the Infinity Cache with written data gains
-// more (379 MB 148 / 83), as its reads then push out no dirty lines.
-constexpr int64_t kStreamTokenHeads = 300000000 / 72;
-
-hipError_t launch_decode(const DecodeArgs& a, int waves, hipStream_t st) {
+hipError_t launch_decode(DecodeArgs a, int waves, hipStream_t st) {
   const int64_t units = (int64_t)a.nlayers * a.B * a.H;
   const int64_t total = units * a.nsplit;
   const int64_t per_xcd = (total + kXcds - 1) / kXcds;
   const int64_t blocks = per_xcd * kXcds;
   const bool vq = (a.flags & kVQjl) != 0;
-  const bool stream = units * a.max_len > kStreamTokenHeads;
+  const bool stream = units * a.max_len > kStreamTokenHeads;   // (the most it can read)
+  a.stream_lengths = (float)((double)kStreamTokenHeads * std::min(a.B, 64) / (double)units);
   auto launch = [&](auto kernel, int w) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(w * 64), 0, st, a, (int)total, (int)per_xcd);
   };

@@ -85,6 +85,7 @@ struct DecodeArgs {
   int append;
   int len_add;
   int wait_limit;          // polls of a decode step's wait for its appends before giving up
+  float stream_lengths;    // sum of (64 at most of) the lengths above which tiles are loaded with the hint (set by the launch)
   DivMagic div_ns, div_h, div_b, div_st;   // by nsplit, H, B and split_tiles
 };
 
@@ -115,7 +116,7 @@ struct DequantArgs {
 hipError_t launch_rope_table(float* cs, int positions, double base, hipStream_t st);
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t st);
 void decode_plan(int units, int max_len, int* waves, int* nsplit, int* split_tiles);
-hipError_t launch_decode(const DecodeArgs& a, int waves, hipStream_t st);
+hipError_t launch_decode(DecodeArgs a, int waves, hipStream_t st);
 hipError_t launch_dequantize(const DequantArgs& a, hipStream_t st);
 // Initial levels of the table calibration (by value: a host array).
 struct LutInit {
