@@ -561,15 +561,36 @@ __device__ __forceinline__ uint32_t nibble_mask(uint32_t m) {
 // in order. In a ragged call sequence b has ceil(T_b / 32) of them; lane i of
 // a wave then holds the running count of groups up to sequence first + i of a
 // window of 64 sequences, and a group's sequence is found by one ballot (the
-// window moves where the group lies outside it).
+// window moves where the group lies outside it). Where there are more windows
+// than one, the block's waves first count their groups into LDS, so that a
+// window is found there (60000 sequences, one in 50 with 64 tokens, one head:
+// 55 us; 694 with windows walked one after the other, 211 in blocks of their own
+// per sequence).
+constexpr int kMaxWindows = 1024;            // (the host keeps B below 2^16)
+
 struct GroupCursor {
   int first, base, end;   // the window's first sequence; groups before and up to the end of the window
   int upto, own;          // per lane: groups up to and of sequence first + lane
 
+  // Groups of sequence b.
+  __device__ __forceinline__ static int groups(const QuantArgs& a, int b) {
+    return b < a.B ? (min(max(a.tokens[b], 0), a.T) + kGroup - 1) / kGroup : 0;
+  }
+
+  // The window that holds a group, found in the groups before each one.
+  __device__ __forceinline__ void find(const QuantArgs& a, const int* before, int windows, int group, int lane) {
+    int lo = 0, hi = windows - 1;              // the last window with at most `group` before it
+    while (lo < hi) {
+      const int half = (lo + hi + 1) >> 1;
+      if (__builtin_amdgcn_readfirstlane(before[half]) <= group) lo = half; else hi = half - 1;
+    }
+    window(a, 64 * lo, __builtin_amdgcn_readfirstlane(before[lo]), lane);
+  }
+
   __device__ __forceinline__ void window(const QuantArgs& a, int f, int before, int lane) {
     first = f;
     base = before;
-    own = f + lane < a.B ? (min(max(a.tokens[f + lane], 0), a.T) + kGroup - 1) / kGroup : 0;
+    own = groups(a, f + lane);
     upto = own;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -620,6 +641,7 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
   __shared__ float s_lev[kPackHeads][2][8];                                           // K and V levels
   __shared__ float s_thr[kPackHeads][2][8];                                           // their t0, t2, t4, t6, t1, t3, t5
   __shared__ int s_asc[kPackHeads][2];                                                // strictly ascending
+  __shared__ int s_before[kMaxWindows + 1];                                           // groups before a window
   // The thread's and the lane's number from a copy that the compiler cannot
   // carry over: what is derived from them is formed where it is used, instead
   // of staying live (and spilled) through the loops.
@@ -637,12 +659,40 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
   // each XCD gets one contiguous eighth of the shares.
   GroupCursor cur{};
   int per_head = a.B * groups_per_seq;
+  const int windows = (a.B + 63) >> 6;
   if (a.tokens) {
-    cur.window(a, 0, 0, lane_of());
-    per_head = cur.end;
-    for (int f = 64; f < a.B; f += 64) {
-      cur.window(a, f, per_head, lane_of());
+    if (windows == 1) {
+      cur.window(a, 0, 0, lane_of());
       per_head = cur.end;
+    } else {
+      for (int w = wave; w < windows; w += kPackWaves) {
+        int n = GroupCursor::groups(a, 64 * w + lane_of());
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+        s_before[w] = n;
+      }
+      __syncthreads();
+      if (wave == 0) {                         // each lane a run of windows
+        const int lane = lane_of(), run = (windows + 63) >> 6, w0 = min(lane * run, windows);
+        const int w1 = min(w0 + run, windows);
+        int own = 0;
+        for (int w = w0; w < w1; ++w) own += s_before[w];
+        int upto = own;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int n = __shfl_up(upto, o, 64);
+          upto += lane >= o ? n : 0;
+        }
+        int before = upto - own;
+        for (int w = w0; w < w1; ++w) {
+          const int n = s_before[w];
+          s_before[w] = before;
+          before += n;
+        }
+        if (lane == 63) s_before[windows] = upto;
+      }
+      __syncthreads();
+      per_head = __builtin_amdgcn_readfirstlane(s_before[windows]);
     }
     if (per_head == 0) return;
   }
@@ -733,8 +783,7 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       int b, j0, Tb;
       if (a.tokens) {
         const int lane = lane_of();
-        if (group < cur.base) cur.window(a, 0, 0, lane);
-        while (group >= cur.end) cur.window(a, cur.first + 64, cur.end, lane);
+        if (group < cur.base || group >= cur.end) cur.find(a, s_before, windows, group, lane);
         const int i = __builtin_ctzll(__builtin_amdgcn_ballot_w64(cur.upto > group));
         b = cur.first + i;
         j0 = (group - __builtin_amdgcn_readlane(cur.upto - cur.own, i)) * kGroup;

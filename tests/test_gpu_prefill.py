@@ -233,3 +233,26 @@ def _residual(x, lut):
     u = x * np.float32(np.float32(8) / np.sqrt(s))
     idx = (u[:, None] > np.float32(0.5) * (lut[1:] + lut[:-1])).sum(1)
     return idx, u - lut[idx]
+
+
+@pytest.mark.parametrize("B,every", [(130, 1), (4097, 7), (9000, 40)])
+def test_ragged_batches_of_thousands_of_sequences(B, every):
+    # more windows of 64 sequences than waves or lanes, most sequences empty,
+    # against calls of 60 sequences
+    T, H = 64, 1
+    g = synth.rng(89)
+    lens = np.where(np.arange(B) % every == every // 2, g.integers(1, T + 1, B), 0)
+    lens[[0, B - 1]] = [5, T]
+    gen = torch.Generator(device="cuda").manual_seed(90)
+    k, v = (torch.randn((1, B, T, H, 64), generator=gen, device="cuda").half() for _ in range(2))
+    case = Case(91, 1, H, 1, T)
+    args = (case.t("pi"), case.t("lut_k"), case.t("lut_v"), case.t("S"))
+    pos, first = torch.zeros(B, dtype=torch.int32).cuda(), torch.arange(B).cuda() * 64
+    tokens = torch.tensor(lens, dtype=torch.int32).cuda()
+    whole, parts = tq.Cache(1, H, B * 64), tq.Cache(1, H, B * 64)
+    tq.quantize_pack(case.params(), whole, k, v, pos, first, *args, seq_tokens=tokens)
+    for b in range(0, B, 60):
+        s = slice(b, b + 60)
+        tq.quantize_pack(case.params(), parts, k[:, s].contiguous(), v[:, s].contiguous(), pos[s].clone(),
+                         first[s].clone(), *args, seq_tokens=tokens[s].clone())
+    assert all(torch.equal(x, y) for x, y in zip(_planes(whole), _planes(parts)))
