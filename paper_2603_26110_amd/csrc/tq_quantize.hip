@@ -726,8 +726,10 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       const Levels L = load_levels((v ? a.lut_v : a.lut_k) + (lh0 + hd) * 8);
       float* lev = s_lev[hd][v];
       float* thr = s_thr[hd][v];
-      lev[0] = L.c0; lev[1] = L.c1; lev[2] = L.c2; lev[3] = L.c3;
-      lev[4] = L.c4; lev[5] = L.c5; lev[6] = L.c6; lev[7] = L.c7;
+      // (a level of 0 as -0: then u - c is +0 for u of either zero)
+      const auto of = [](float c) { return c == 0.0f ? -0.0f : c; };
+      lev[0] = of(L.c0); lev[1] = of(L.c1); lev[2] = of(L.c2); lev[3] = of(L.c3);
+      lev[4] = of(L.c4); lev[5] = of(L.c5); lev[6] = of(L.c6); lev[7] = of(L.c7);
       thr[0] = L.t0; thr[1] = L.t2; thr[2] = L.t4; thr[3] = L.t6; thr[4] = L.t1; thr[5] = L.t3; thr[6] = L.t5;
       s_asc[hd][v] = levels_ascending(L) ? 1 : 0;
     }
@@ -828,9 +830,9 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       if (!paper) {
         sb = projected_signs<VQJL>(x, qo.g, s_sh, s_sl, snmax, a.qjl_s, lane);
       } else {
-        uint32_t neg[2] = {0u, 0u};            // (the sign of r: -0 is not below 0, nor is a NaN of either sign)
+        uint32_t neg[2] = {0u, 0u};            // (the sign of r, never -0; a NaN of either sign is not below 0)
 #pragma unroll
-        for (int i = kDim - 1; i >= 0; --i) neg[i >> 5] = push_sign(neg[i >> 5], fminf(x[i] + 0.0f, INFINITY));
+        for (int i = kDim - 1; i >= 0; --i) neg[i >> 5] = push_sign(neg[i >> 5], fminf(x[i], INFINITY));
         sb = ~(((uint64_t)neg[1] << 32) | neg[0]);
       }
 

@@ -155,12 +155,14 @@ def test_short_sequences_in_a_batch_equal_each_alone(T, lens, flags, io):
 
 @pytest.mark.parametrize("flags", [tq.QJL_PAPER, tq.QJL_PAPER | tq.V_QJL])
 def test_element_signs_of_vectors_with_nan(flags):
-    # sign_i = !(r_i < 0): a NaN residual, of either sign bit, has sign 1. Against
-    # calls of 16 tokens, which another kernel takes.
+    # sign_i = !(r_i < 0): a NaN residual, of either sign bit, and a zero one have
+    # sign 1. Against calls of 16 tokens, which another kernel takes.
     T, H = 96, 2
     flags |= tq.INPUT_ROTATED
     case = Case(84, 1, H, 1, T, io="f32", flags=flags, slots=128)
+    case.lut_k[0, 1, 3] = case.lut_v[0, 1, 4] = 0.0          # r = -0 - 0 for a coordinate of -0
     for x in (case.k, case.v):
+        x[0, 0, ::2, :, 20:24] = -0.0
         x[0, 0, 3::16, :, 5] = np.inf                        # u = inf * 0 there
         x[0, 0, 5::16, :, 7] = np.nan
         x.view(np.uint32)[0, 0, 7::16, :, 9] = 0xFFC00000     # NaN with the sign bit set
