@@ -1216,12 +1216,6 @@ void quantize_batch_kernel(QuantArgs a, int total_blocks, int per_xcd, int chunk
   }
 }
 
-// quantize_batch_kernel takes a call of short sequences from this many tokens
-// per (layer, head), and token-heads in all, on. One token each (fp16, us, this
-// kernel / quantize_vectors_kernel): 64 tokens x 20 heads 10.4 / 8.6, 12 x 180
-// 11.5 / 13.0, 4 x 1440 27.7 / 24.5, 8 x 660 23.8 / 22.9, 8 x 1440 39 / 43.
-constexpr int64_t kBatchTokenHeads = 2048, kBatchTokens = 12;
-
 // Its tokens per block: a pass takes 16 of a (layer, head); as many passes as
 // bring the blocks down to the two per compute unit that run at once (a pass
 // more costs less than a second staging).
@@ -1229,6 +1223,25 @@ static int batch_chunk(int64_t heads, int64_t tokens) {
   const int64_t passes = (tokens + 15) / 16;
   const int64_t per_head = std::max<int64_t>(1, std::min(passes, 2 * (int64_t)kComputeUnits / heads));
   return (int)((passes + per_head - 1) / per_head * 16);
+}
+
+// Whether quantize_batch_kernel takes a call of short sequences: from 12 tokens
+// per (layer, head) on, where the token-heads fill its passes. A pass costs it
+// about the same however few of its 16 tokens there are; up to one block per
+// compute unit it waits on nothing else. Without the rotation or the projection
+// (`without` of the two) the other kernel has less to stage per token, and the
+// line lies higher. One token per sequence (fp16, us, this kernel /
+// quantize_vectors_kernel): one block per compute unit at most, 180 heads x 12
+// tokens 11 / 12, 140 x 16 12 / 12; one pass of more blocks, 140 x 18 15 / 13,
+// 180 x 18 16 / 15, 220 x 17 16 / 17, 340 x 12 16 / 18; two passes, 260 x 20
+// 24 / 21, 300 x 20 25 / 24, 340 x 20 25 / 27, 400 x 17 24 / 27. In the
+// per-element form 180 x 16 12.4 / 11.6, 256 x 12 12.4 / 12.2, 20 x 200 15.5 /
+// 14.6, 256 x 20 15.7 / 17.5, 340 x 20 23.5 / 22.4, 400 x 20 25.2 / 25.6.
+static bool batch_pays(int64_t heads, int64_t tokens, int without) {
+  const int64_t passes = batch_chunk(heads, tokens) / 16, blocks = heads * ((tokens + 16 * passes - 1) / (16 * passes));
+  const int64_t least = passes == 1 && blocks <= kComputeUnits ? (without == 1 ? 3100 : 2048)
+                                                               : (600 + 3000 * passes) * (4 + without) / 4;
+  return tokens >= 12 && heads * tokens >= least;
 }
 
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t st) {
@@ -1250,7 +1263,8 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t st) {
   } else {
     const int64_t heads = (int64_t)a.nlayers * a.H, tokens = (int64_t)a.B * a.T;
     const uint32_t total = (uint32_t)(heads * tokens);
-    if (total >= kBatchTokenHeads && tokens >= kBatchTokens) {
+    const int without = ((a.flags & kInputRotated) != 0) + ((a.flags & kQjlPaper) != 0);
+    if (batch_pays(heads, tokens, without)) {
       const int chunk = batch_chunk(heads, tokens);
       const int chunks = (int)((tokens + chunk - 1) / chunk), blocks = (int)(heads * chunks);
       const int per_xcd = (blocks + kXcds - 1) / kXcds;
