@@ -57,8 +57,9 @@ hipError_t launch_rope_table(float* cs, int positions, double base, hipStream_t 
 // hi = fp16(v), lo = fp16(v - hi) and three products hi*hi + hi*lo + lo*hi,
 // which carries a product to about 2^-21 relative. Each vector is first scaled
 // by a power of two (exact) so that its largest entry lies in [1, 2), and each
-// row of S likewise, which keeps the parts in fp16's range. Values in fp16 are
-// their own high part: they are neither scaled nor split, and have no low part.
+// row of S to norm 8 (the split takes the exact product), which keeps the parts
+// in fp16's range. Values in fp16 are their own high part: they are neither
+// scaled nor split, and have no low part.
 // Instruction layout (lane l, n = l % 32, h = l / 32; verified on gfx950):
 //   A lane values A[n][8h + j], B lane values B[8h + j][n] (j = 0..7),
 //   D register r D[8 (r/4) + 4h + r%4][n].
@@ -395,18 +396,18 @@ __device__ __forceinline__ uint32_t nibbles_to_bytes(uint32_t x) {
 // Projected QJL sign bits of the wave's residuals (lane l: r of its key, or
 // with BOTH its key or value): bit i = !(p_i < 0) for p_i the binary32 fma
 // chain over k ascending of S[i][k] r_k (the exact quantizer step).
-// p~ = (sigma_i S_i) . (s r) comes from the matrix cores (sigma_i, s: the
-// row's and the vector's power-of-two scales; s brings ||r|| = g into [1, 2)),
-// and its sign is taken where |p~_i| > kSignBand max_i ||sigma_i S_i|| ||s r||.
+// p~ = (sigma_i S_i) . (s r) comes from the matrix cores (sigma_i makes the
+// row's norm 8; the power of two s brings ||r|| = g into [1, 2)), and its sign
+// is taken where |p~_i| > kSignBand max_i ||sigma_i S_i|| ||s r||.
 // There it is the chain's, whatever order and rounding the matrix cores sum a
 // row's 192 products in. In units of ||sigma_i S_i|| ||s r||: where the signs
 // differ the exact sum is next to 0, so its partial sums are at most 1/2
 // (Cauchy-Schwarz on the two parts); one addition per product, truncated to
 // fp32, then errs by up to 192 x 2^-24 = 2^-16.4, the split products by
 // 2^-20.4, the fp16 spacing below 2^-14 by 2^-21 and the chain by 2^-19:
-// 2^-16.1 in all, and kSignBand is twice that. (2^-16 would save 0.7 us of
-// 13.1 for 1024 tokens of 20 heads, with no room; 2^-14 cost 1.6 us more.)
-// The smallest
+// 2^-16.1 in all, and kSignBand is twice that. (Rows of equal norm keep the
+// band no wider than each row needs: 1024 tokens of 20 heads 12.2 us, 13.1 with
+// rows scaled by powers of two.) The smallest
 // |p~_i| tells whether any coordinate lies inside that band (snmax: the
 // largest row norm, infinite if a row is not finite); only then are the rows
 // found, and recomputed with the chain from S in memory for all the wave's
@@ -733,7 +734,7 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       thr[0] = L.t0; thr[1] = L.t2; thr[2] = L.t4; thr[3] = L.t6; thr[4] = L.t1; thr[5] = L.t3; thr[6] = L.t5;
       s_asc[hd][v] = levels_ascending(L) ? 1 : 0;
     }
-    // The rows of S scaled by powers of two sigma_i, and their norms, by the
+    // The rows of S scaled by sigma_i, and their norms, by the
     // last four waves: four threads per row, which combine their maxima and
     // sums by shuffles.
     if (const int t = thread_of() - (kPackThreads - 256); first && t >= 0) {
@@ -750,7 +751,7 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       for (int k = 0; k < 16; ++k) mx = fmaxf(mx, fabsf(sv[k]));
       mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-      const float sig = unit_scale(mx);        // row r's scale (the same in its four threads)
+      float sig = unit_scale(mx);              // row r's scale (the same in its four threads)
       float ss = 0.0f;
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
@@ -759,7 +760,11 @@ void quantize_tiles_kernel(QuantArgs a, int blocks, int groups_per_seq, DivMagic
       }
       ss += __shfl_xor(ss, 1, 64);
       ss += __shfl_xor(ss, 2, 64);
-      if ((t & 3) == 0) s_Sn[r] = sqrtf(ss);   // bounds the guard band only
+      // Norm 8, so that the largest row's is every row's (rows whose norm is
+      // not of the usual size keep the power of two).
+      const float norm = sqrtf(ss), even = ss >= 1.0f && ss < 0x1p20f && sig < 0x1p100f ? 8.0f / norm : 1.0f;
+      sig *= even;
+      if ((t & 3) == 0) s_Sn[r] = norm * even; // bounds the guard band only
 #pragma unroll
       for (int k = 0; k < 16; k += 8) {
         half8 hi, lo;
