@@ -349,7 +349,8 @@ TQ_API tq_status tq_calibrate_rotation(const float* x, int32_t nheads, int32_t n
  * vectors, x^ = Pi x in fp64 (x^ = x when pi is NULL; a zero vector gives
  * zeros, as in the quantizer). Each iteration assigns u to level
  * #{m : u > (c_m + c_{m+1})/2}, replaces every level by the mean of its cell
- * (fp64 sums; an empty cell keeps its level), sorts the levels and stops
+ * (sums of the fp64 coordinates in 62 bits, or in fp64 where a level is so
+ * small that it needs them; an empty cell keeps its level), sorts the levels and stops
  * once the largest level change is below tol, or after max_iter iterations.
  *   x        device [nheads][ncal][64] fp32: post-RoPE keys for the K table,
  *            values for the V table.

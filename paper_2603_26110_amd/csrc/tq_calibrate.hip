@@ -227,8 +227,9 @@ hipError_t launch_calibrate(const float* x, int nheads, int ncal, float* pi_out,
 // vectors, contracts k in the order that leaves each lane 16 consecutive
 // elements to load (step s of lane group g = lane / 16 takes k = 16 g + s, on
 // both operands), and holds its share of Pi, 64 doubles per lane, in registers
-// for the whole call. Every lane ends with 16 coordinates of vector lane % 16; the
-// norm is a sum over them and the four lanes that hold the vector. A walk of
+// for the whole call (calibrate_lut_kernel needs more than the 256 that two waves
+// per SIMD leave, and spills 33). Every lane ends with 16 coordinates of vector
+// lane % 16; the norm is a sum over them and the four lanes that hold the vector. A walk of
 // 4096 vectors takes 0.18 ms (calibrate_ebar_kernel) to 0.23 ms, of which the
 // matrix products are about 0.13 ms at the rate that a large fp64 product
 // reaches per compute unit; one lane per coordinate with the rows of Pi read

@@ -610,19 +610,24 @@ struct GroupCursor {
 // its waves then take the groups of these in turn, with no barrier between
 // (layer, head)s.
 //
-// What bounds it: the vector ALU, 1,660 instructions per group at three waves
-// per SIMD (168 registers), and what three waves leave uncovered of their load
-// and LDS latencies. Keys and values side by side in one wave (half the lanes
-// each) make one instruction stream of both, halve the registers of the
-// projected signs (only keys have them), and a group's keys and values end
+// What bounds it: the vector ALU, 1,690 instructions per group at three waves
+// per SIMD (168 registers): 60 % of the issue slots over 1024 tokens of 33
+// layers (the matrix cores are busy 18 %), and what three waves leave uncovered
+// of their load and LDS latencies. Keys and values side by side in one wave
+// (half the lanes each) make one instruction stream of both, halve the registers
+// of the projected signs (only keys have them), and a group's keys and values end
 // together; that the value lanes run the residual steps unused costs less.
 // Four waves per SIMD would need 128 registers: the compiler then spills 40,
 // and the spills' 78 MB of traffic cost more than the fourth wave gives (131
-// against 112 us in blocks of 4 waves).
-// fp16, 20 heads: 1024 tokens of 33 layers 102 us, of one layer 12.9 us, one
-// layer of 64 sequences of 50 to 1024 tokens 112 us; 127, 20.6 and 210 us in
-// blocks of 4 waves of which each took 64 tokens of one sequence, first the
-// keys and then the values: partly filled blocks and a chain twice as long.
+// against 112 us in blocks of 4 waves). At 168 the forms with V signs, whose
+// projections double, spill 21 to 24 (88 to 100 B of scratch per lane), the fp32
+// one without V signs 1, the others none; all keep 11 to 33 scalars in vector
+// lanes.
+// fp16, 20 heads: 1024 tokens of 33 layers 95 us (with V signs 122), of one
+// layer 12.2 us, one layer of 64 sequences of 50 to 1024 tokens 111 us; 115 (161),
+// 20.0 and 198 us in blocks of 4 waves of which each took 64 tokens of one
+// sequence, first the keys and then the values: partly filled blocks and a chain
+// twice as long.
 constexpr int kPackWaves = 12;
 constexpr int kPackThreads = kPackWaves * 64;
 constexpr int kPackHeads = 4;       // (layer, head)s staged at a time
@@ -1063,8 +1068,10 @@ __device__ __forceinline__ void row_dots(const float* m, int i, float (&x)[NT]) 
 // reads of the matrix rows, and their norm chains run in different lanes (lane
 // t runs vector t's).
 //
-// What bounds it: the fma chains and the waits between them, at four waves per
-// SIMD. fp16, 60 tokens x 1440 (layer, head)s 115 us, 8 tokens of 64 sequences
+// What bounds it: the vector ALU, 63 % of the issue slots at four waves per SIMD
+// (60 tokens x 1440 (layer, head)s), and the waits between the fma chains. At the
+// 128 registers of four waves it spills 24 (100 B of scratch per lane) and keeps
+// 41 scalars in vector lanes. fp16, 60 tokens x 1440 (layer, head)s 115 us, 8 tokens of 64 sequences
 // x 20 heads 23.5 us; 324 and 39.1 us in quantize_vectors_kernel, whose blocks
 // stage 32 KB per token and merge every value nibble by two atomics of its own
 // (alone 65 of the 180 us that this kernel took with them).
