@@ -623,9 +623,9 @@ struct GroupCursor {
 // projections double, spill 21 to 24 (88 to 100 B of scratch per lane), the fp32
 // one without V signs 1, the others none; all keep 11 to 33 scalars in vector
 // lanes.
-// fp16, 20 heads: 1024 tokens of 33 layers 95 us (with V signs 122), of one
-// layer 12.2 us, one layer of 64 sequences of 50 to 1024 tokens 111 us; 115 (161),
-// 20.0 and 198 us in blocks of 4 waves of which each took 64 tokens of one
+// fp16, 20 heads, repeated on the same buffers: 1024 tokens of 33 layers 95 us
+// (with V signs 122), of one layer 12.2 us, one layer of 64 sequences of 50 to
+// 1024 tokens 100 us; 115 (161), 20.0 and 198 us in blocks of 4 waves of which each took 64 tokens of one
 // sequence, first the keys and then the values: partly filled blocks and a chain
 // twice as long.
 constexpr int kPackWaves = 12;
