@@ -625,9 +625,9 @@ struct GroupCursor {
 // lanes.
 // fp16, 20 heads, repeated on the same buffers: 1024 tokens of 33 layers 95 us
 // (with V signs 122), of one layer 12.2 us, one layer of 64 sequences of 50 to
-// 1024 tokens 100 us; 115 (161), 20.0 and 198 us in blocks of 4 waves of which each took 64 tokens of one
-// sequence, first the keys and then the values: partly filled blocks and a chain
-// twice as long.
+// 1024 tokens 100 us; 115 (161), 20.0 and 198 us in blocks of 4 waves of which
+// each took 64 tokens of one sequence, first the keys and then the values: partly
+// filled blocks and a chain twice as long.
 constexpr int kPackWaves = 12;
 constexpr int kPackThreads = kPackWaves * 64;
 constexpr int kPackHeads = 4;       // (layer, head)s staged at a time
